@@ -66,6 +66,9 @@ struct dgw_ctx {
   void *d_DrT = nullptr, *d_DsT = nullptr, *d_DtT = nullptr, *d_LIFTT = nullptr;
   void *d_Avol = nullptr, *d_Alift = nullptr;   // MFMA operator fragments
   void *d_Alf = nullptr;                         // per-face lift fragments
+  void *d_Asym = nullptr;                        // symmetry-component fragments (sym.h)
+  uint32_t *d_symnode = nullptr;
+  int32_t *d_fslot = nullptr;
   double *d_M = nullptr;
   void *d_q[2] = {nullptr, nullptr};
   void *d_res = nullptr;
@@ -186,6 +189,9 @@ inline void stage_args(const dgw_ctx *c, dgw::StageArgs<real> &a, const void *in
   a.Avol = (const real *)c->d_Avol;
   a.Alift = (const real *)c->d_Alift;
   a.Alf = (const real *)c->d_Alf;
+  a.Asym = (const real *)c->d_Asym;
+  a.symnode = c->d_symnode;
+  a.fslot = c->d_fslot;
   a.fmask = c->d_fmask;
   a.K = c->mesh.K;
   a.shot_stride = c->mesh.K * 9 * c->R.Np;

@@ -35,28 +35,222 @@
 
 #include "dgw_internal.h"
 #include "stage_common.h"
+#include "sym.h"
 
 namespace dgw {
 
 namespace {
 
 constexpr int kThreads = 256;
+// Whether the matrix-core form of an order and precision works in symmetry
+// components (phase3_sym): FP64 from order 4.  FP32 keeps the nodal form's
+// order of summation, and with it its results to the last bit.
+template <int N, typename real>
+constexpr bool kSymForm = N >= 4 && sizeof(real) == 8;
 using namespace stagec;
 
-// Phase 3 on the matrix cores.  By linearity the element's metric and
-// material factors move to the input side: every right-hand-side component
-// is rhs_k = sum_a D_a u_{k,a} + LIFT F_k, with u_{k,a} = sum_m c_{k,a,m}
-// q_{f(k,m)} a per-node combination of at most three fields (for example
-// u_{vx,a} = (1/rho) sum_b X^-1[a][b] sigma_{xb} and
+// Residual and update of a block's contiguous span by 16-byte vectors; the
+// right-hand side comes from LDS in the block's (element, field, node) order.
+//
+// Streaming at order >= 4: the residual (read and written once per stage)
+// and the FP64 output state move with non-temporal loads and stores, so
+// they do not evict the neighbour traces and operators.  Measured on the
+// order-4 82944-element workload (whose streams exceed the 256 MB
+// last-level cache): FP64 370 -> 351 us, FP32 213 -> 204 us (FP32 keeps
+// its output state cached, which measured faster).  The order-3
+// 24576-element gradient workload fits that cache and ran 5% slower with
+// them, so lower orders keep ordinary accesses.
+template <int N, typename real, int BE>
+struct Update {
+  static constexpr int Np = Sz<N>::Np;
+  static constexpr bool kStream = N >= 4;
+  using SP = Span16<real>;
+  static constexpr int UV = (BE * 9 * Np / SP::VW + kThreads - 1) / kThreads;
+  SP sp;
+  bool first;
+  real *rs, *qo;
+  int tl0;
+  typename SP::vec rv[UV];
+  real rh, rt;
+
+  // residual loads of this thread's update items, all issued together
+  __device__ __forceinline__ Update(const StageArgs<real> &A, int64_t k0, int shot, int nE,
+                                    real *qout, real *res, int tid)
+      : sp(shot * A.shot_stride + k0 * 9 * Np, nE * 9 * Np) {
+    first = A.rk_a == 0.0;
+    rs = res + k0 * 9 * Np;
+    qo = qout + k0 * 9 * Np;
+#pragma unroll
+    for (int u = 0; u < UV; ++u) {
+      const int j = tid + u * kThreads;
+      if (!first && j < sp.nv) {
+        const typename SP::vec *rp = (const typename SP::vec *)(rs + sp.hd) + j;
+        if constexpr (kStream)
+          rv[u] = __builtin_nontemporal_load(rp);
+        else
+          rv[u] = *rp;
+      }
+      else rv[u] = typename SP::vec{};
+    }
+    tl0 = sp.hd + SP::VW * sp.nv;
+    rh = (!first && tid < sp.hd) ? rs[tid] : (real)0;
+    rt = (!first && tid < sp.tl) ? rs[tl0 + tid] : (real)0;
+  }
+
+  // point source and LSERK update over the contiguous span
+  __device__ __forceinline__ void apply(const StageArgs<real> &A, const real *sq,
+                                        const real *sfl, const double *ssig, int nE,
+                                        int64_t k0, int shot, int64_t step, int tid) {
+    const real ra = (real)A.rk_a, rb = (real)A.rk_b, rdt = (real)A.dt;
+    const int64_t es = (int64_t)A.src_elem[shot] - k0;   // source element in block
+    double s = 0.0;
+    const double *spar = A.src_par + 10 * shot;
+    if (es >= 0 && es < nE)
+      s = ricker_d(((double)step + A.rk_c) * A.dt, spar[6], spar[7], spar[8]);
+    auto update = [&](int t, real rold) -> real2v<real> {
+      real rhs = sfl[t];
+      const int e = t / (9 * Np), ci = t - e * 9 * Np, c = ci / Np, i = ci - c * Np;
+      if (e == es && c >= 3) rhs += (real)(s * spar[c - 3] * A.src_vec[shot * Np + i]);
+      if (A.sponge) rhs -= (real)ssig[e] * sq[t];
+      const real rn = first ? rdt * rhs : ra * rold + rdt * rhs;
+      return {rn, sq[t] + rb * rn};
+    };
+#pragma unroll
+    for (int u = 0; u < UV; ++u) {
+      const int j = tid + u * kThreads;
+      if (j >= sp.nv) continue;
+      const int b = sp.hd + SP::VW * j;
+      typename SP::vec nr, nq;
+#pragma unroll
+      for (int l = 0; l < SP::VW; ++l) {
+        const real2v<real> o = update(b + l, rv[u][l]);
+        nr[l] = o.r;
+        nq[l] = o.q;
+      }
+      if constexpr (kStream) {
+        __builtin_nontemporal_store(nr, (typename SP::vec *)(rs + b));
+        if constexpr (sizeof(real) == 8)
+          __builtin_nontemporal_store(nq, (typename SP::vec *)(qo + b));
+        else
+          *(typename SP::vec *)(qo + b) = nq;
+      } else {
+        *(typename SP::vec *)(rs + b) = nr;
+        *(typename SP::vec *)(qo + b) = nq;
+      }
+    }
+    if (tid < sp.hd) {
+      const real2v<real> o = update(tid, rh);
+      if constexpr (kStream)
+        __builtin_nontemporal_store(o.r, rs + tid);
+      else
+        rs[tid] = o.r;
+      qo[tid] = o.q;
+    }
+    if (tid < sp.tl) {
+      const real2v<real> o = update(tl0 + tid, rt);
+      if constexpr (kStream)
+        __builtin_nontemporal_store(o.r, rs + tl0 + tid);
+      else
+        rs[tl0 + tid] = o.r;
+      qo[tl0 + tid] = o.q;
+    }
+  }
+};
+
+// A column (element, field k) of the block's right-hand side.  By linearity
+// the element's metric and material factors move to the input side: every
+// component is rhs_k = sum_a D_a u_{k,a} + LIFT F_k, with
+// u_{k,a} = sum_m c_{a,m} q_{f(m)} a per-node combination of at most three
+// fields (for example u_{vx,a} = (1/rho) sum_b X^-1[a][b] sigma_{xb} and
 // u_{sxx,a} = (lambda + 2 mu) X^-1[a][0] vx + lambda X^-1[a][1] vy +
-// lambda X^-1[a][2] vz).  So the block's right-hand side is one GEMM,
-// rhs[i][(e,k)] = [Dr Ds Dt LIFT][i][.] x [u_r; u_s; u_t; F][.][(e,k)],
-// whose operator side is shared by all elements: the operator fragments are
-// pre-arranged in HBM in MFMA lane order (L1/L2-resident), the data side is
-// formed in registers from the LDS tile.  Each wave owns 16 columns
-// (element, field); rows are nodes.  The accumulators go through LDS (the
-// flux buffer, dead by then) so that the residual loads, the update and the
-// stores run over the block's contiguous span, fully coalesced.
+// lambda X^-1[a][2] vz).
+template <typename real>
+struct Column {
+  int f[3];
+  real c[3][3];
+};
+
+template <typename real, bool AN>
+__device__ __forceinline__ void column_setup(const StageArgs<real> &A, const double *gm,
+                                             int64_t k0e, int k, Column<real> &o) {
+  // input-side coefficients of this column, c[a][m] = s_m X^-1[a][x_m],
+  // with the material factor s_m and the metric column x_m of each of
+  // the three combined fields f_m given per component k by packed tables
+  // (branch-free: the sixteen lanes of a column tile hold different k):
+  //   k = 0..2 (vx, vy, vz):   f = sigma row k, s = 1/rho, x = (0, 1, 2)
+  //   k = 3..5 (sxx..szz):      f = (vx, vy, vz), s = lambda + 2 mu on
+  //                             x = k - 3, lambda elsewhere, x = (0, 1, 2)
+  //   k = 6 (syz): f = (vy, vz), s = mu, x = (2, 1)
+  //   k = 7 (sxz): f = (vx, vz), s = mu, x = (2, 0)
+  //   k = 8 (sxy): f = (vx, vy), s = mu, x = (1, 0)
+  // fields (4 bits per k, m = 0, 1, 2)
+  constexpr uint64_t F0 = 0x001000783ull, F1 = 0x122111648ull, F2 = 0x210222567ull;
+  // metric columns (2 bits per k) and material factor ids (3 bits per k:
+  // 0 1/rho, 1 lambda + 2 mu, 2 lambda, 3 mu, 4 zero)
+  constexpr uint32_t X0 = 0x1a000u, X1 = 0x01555u, X2 = 0x2aaaau;
+  constexpr uint32_t S0 = 0x36d2200u, S1 = 0x36d1400u, S2 = 0x490a400u;
+  int f0 = (int)((F0 >> (4 * k)) & 15), f1 = (int)((F1 >> (4 * k)) & 15),
+      f2 = (int)((F2 >> (4 * k)) & 15);
+  const real ri = (real)gm[M_RHOINV], la = (real)gm[M_LAM], mu = (real)gm[M_MU];
+  const real l2 = la + 2 * mu;
+  auto fac = [&](uint32_t S) -> real {
+    const int id = (int)((S >> (3 * k)) & 7);
+    return id == 0 ? ri : id == 1 ? l2 : id == 2 ? la : id == 3 ? mu : (real)0;
+  };
+  const real s0 = fac(S0), s1 = fac(S1), s2 = fac(S2);
+  const int x0 = (int)((X0 >> (2 * k)) & 3), x1 = (int)((X1 >> (2 * k)) & 3),
+            x2 = (int)((X2 >> (2 * k)) & 3);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const real r0 = (real)gm[M_XINV + 3 * a], r1 = (real)gm[M_XINV + 3 * a + 1],
+               r2 = (real)gm[M_XINV + 3 * a + 2];
+    auto pick = [&](int x) { return x == 0 ? r0 : x == 1 ? r1 : r2; };
+    o.c[a][0] = s0 * pick(x0);
+    o.c[a][1] = s1 * pick(x1);
+    o.c[a][2] = s2 * pick(x2);
+  }
+  if constexpr (AN) {
+    // anisotropic stress rows (k >= 3, Voigt row I = k - 3): the fields
+    // are (vx, vy, vz) and c[a][m] = sum_b C[I][voigt(m, b)] X^-1[a][b]
+    // (selects, so the column setup stays branch-free)
+    const bool st = k >= 3;
+    const int I = st ? k - 3 : 0;
+    const double *Cu = A.aniso + k0e * DGW_ANI + A_C;
+    real cr[6];
+#pragma unroll
+    for (int J = 0; J < 6; ++J) {
+      const int i = I < J ? I : J, j = I < J ? J : I;   // upper triangle
+      cr[J] = (real)Cu[i * (11 - i) / 2 + j];
+    }
+    constexpr int VG[3][3] = {{0, 5, 4}, {5, 1, 3}, {4, 3, 2}};   // voigt(m, b)
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        real v = 0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) v += cr[VG[m][b]] * (real)gm[M_XINV + 3 * a + b];
+        o.c[a][m] = st ? v : o.c[a][m];
+      }
+    f0 = st ? 0 : f0;
+    f1 = st ? 1 : f1;
+    f2 = st ? 2 : f2;
+  }
+  o.f[0] = f0;
+  o.f[1] = f1;
+  o.f[2] = f2;
+}
+
+// Phase 3 on the matrix cores in nodal form: the block's right-hand side
+// is one GEMM, rhs[i][(e,k)] = [Dr Ds Dt LIFT][i][.] x
+// [u_r; u_s; u_t; F][.][(e,k)], whose operator side is shared by all
+// elements: the operator fragments are pre-arranged in HBM in MFMA lane
+// order (L1/L2-resident), the data side is formed in registers from the LDS
+// tile.  Each wave owns one or two tiles of 16 columns (element, field) and
+// feeds both from every fragment it loads; rows are nodes.  The accumulators
+// go through LDS (the flux buffer, dead by then) so that the residual loads,
+// the update and the stores run over the block's contiguous span, fully
+// coalesced.
 template <int N, typename real, int BE, bool AN>
 __device__ __forceinline__ void phase3_mfma(const StageArgs<real> &A, const real *sq,
                                             real *sfl, const double *smeta,
@@ -66,291 +260,238 @@ __device__ __forceinline__ void phase3_mfma(const StageArgs<real> &A, const real
   using M = Mma<real>;
   using v4 = typename M::v4;
   constexpr int Np = Sz<N>::Np, NF = 4 * Sz<N>::Nfp;
-  constexpr int MT = (Np + 15) / 16;        // row tiles of 16 nodes
-  constexpr int KS = (Np + 3) / 4;          // k-steps per reference direction
-  constexpr int KL = NF / 4;                // k-steps of the lift (4 Nfp % 4 == 0)
-  constexpr int NT = (9 * BE + 15) / 16;    // column tiles
+  constexpr int MT = (Np + 15) / 16;          // row tiles of 16 nodes
+  constexpr int KS = (Np + 3) / 4;            // k-steps per reference direction
+  constexpr int KL = NF / 4;                  // k-steps of the lift (4 Nfp % 4 == 0)
+  constexpr int NT = (9 * BE + 15) / 16;      // column tiles
+  constexpr int NW = kThreads / 64;
+  constexpr int HT = (NT + NW - 1) / NW;      // column tiles per wave
   static_assert(9 * Np <= 9 * NF, "the flux buffer holds the right-hand side");
-  const int lane = tid & 63, g = lane >> 4;
-  const int span = nE * 9 * Np;
-  // Streaming at order >= 4: the residual (read and written once per stage)
-  // and the FP64 output state move with non-temporal loads and stores, so
-  // they do not evict the neighbour traces and operators.  Measured on the
-  // order-4 82944-element workload (whose streams exceed the 256 MB
-  // last-level cache): FP64 370 -> 351 us, FP32 213 -> 204 us (FP32 keeps
-  // its output state cached, which measured faster).  The order-3
-  // 24576-element gradient workload fits that cache and ran 5% slower with
-  // them, so lower orders keep ordinary accesses.
-  constexpr bool kStream = N >= 4;
-  const bool first = A.rk_a == 0.0;
-  // residual loads of this thread's update items (16-byte vectors over the
-  // block's contiguous span), issued first
-  using SP = Span16<real>;
-  constexpr int UV = (BE * 9 * Np / SP::VW + kThreads - 1) / kThreads;
-  const SP sp(shot * A.shot_stride + k0 * 9 * Np, span);
-  real *rs = res + k0 * 9 * Np, *qo = qout + k0 * 9 * Np;
-  v4 acc[NT > 4 ? 2 : 1][MT];
-  int ntl = 0;
-  if constexpr (!AN && NT == 8) {
-    // eight column tiles: each wave takes tiles w and w + 4 and feeds both
-    // from every operator fragment it loads (two MFMA chains per fragment)
-    const real *q0v[2], *q1v[2], *q2v[2], *flv[2];
-    real cv[2][3][3];
+  const int lane = tid & 63, g = lane >> 4, w = tid >> 6;
+  v4 acc[HT][MT];
+  if (w < NT) {
+    const real *qf[HT][3], *fl[HT];
+    Column<real> C[HT];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int nt = (tid >> 6) + 4 * h;
-      const int col = nt * 16 + (lane & 15);
+    for (int h = 0; h < HT; ++h) {
+      const int col = (w + h * NW) * 16 + (lane & 15);
       const bool cok = col < 9 * nE;
       const int e = cok ? col / 9 : 0, k = cok ? col - 9 * (col / 9) : 0;
-      const real *qe = sq + e * 9 * Np;
-      const double *gm = smeta + e * DGW_META;
-      // the same packed column tables as the one-tile path below
-      constexpr uint64_t F0 = 0x001000783ull, F1 = 0x122111648ull, F2 = 0x210222567ull;
-      constexpr uint32_t X0 = 0x1a000u, X1 = 0x01555u, X2 = 0x2aaaau;
-      constexpr uint32_t S0 = 0x36d2200u, S1 = 0x36d1400u, S2 = 0x490a400u;
-      const int f0 = (int)((F0 >> (4 * k)) & 15), f1 = (int)((F1 >> (4 * k)) & 15),
-                f2 = (int)((F2 >> (4 * k)) & 15);
-      const real ri = (real)gm[M_RHOINV], la = (real)gm[M_LAM], mu = (real)gm[M_MU];
-      const real l2 = la + 2 * mu;
-      auto fac = [&](uint32_t S) -> real {
-        const int id = (int)((S >> (3 * k)) & 7);
-        return id == 0 ? ri : id == 1 ? l2 : id == 2 ? la : id == 3 ? mu : (real)0;
-      };
-      const real s0 = fac(S0), s1 = fac(S1), s2 = fac(S2);
-      const int x0 = (int)((X0 >> (2 * k)) & 3), x1 = (int)((X1 >> (2 * k)) & 3),
-                x2 = (int)((X2 >> (2 * k)) & 3);
+      column_setup<real, AN>(A, smeta + e * DGW_META, k0 + e, k, C[h]);
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const real r0 = (real)gm[M_XINV + 3 * a], r1 = (real)gm[M_XINV + 3 * a + 1],
-                   r2 = (real)gm[M_XINV + 3 * a + 2];
-        auto pick = [&](int x) { return x == 0 ? r0 : x == 1 ? r1 : r2; };
-        cv[h][a][0] = s0 * pick(x0);
-        cv[h][a][1] = s1 * pick(x1);
-        cv[h][a][2] = s2 * pick(x2);
-      }
-      q0v[h] = qe + f0 * Np;
-      q1v[h] = qe + f1 * Np;
-      q2v[h] = qe + f2 * Np;
-      flv[h] = sfl + (e * 9 + k) * NF;
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
+      for (int m = 0; m < 3; ++m) qf[h][m] = sq + (e * 9 + C[h].f[m]) * Np;
+      fl[h] = sfl + (e * 9 + k) * NF;
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) acc[h][mt] = v4{0, 0, 0, 0};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const real *Ab = A.Avol + (size_t)a * KS * MT * 64 + lane + oz;
-      for (int ks = 0; ks < KS; ++ks) {
-        const int j = 4 * ks + g, jj = j < Np ? j : Np - 1;
-        real b[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const real v = cv[h][a][0] * q0v[h][jj] + cv[h][a][1] * q1v[h][jj] +
-                         cv[h][a][2] * q2v[h][jj];
-          b[h] = j < Np ? v : (real)0;
-        }
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          const real af = Ab[(ks * MT + mt) * 64];
-          acc[0][mt] = M::mma(af, b[0], acc[0][mt]);
-          acc[1][mt] = M::mma(af, b[1], acc[1][mt]);
-        }
-      }
     }
-    const real *Al = A.Alift + lane + oz;
-    for (int ks = 0; ks < KL; ++ks) {
-      const real b0 = flv[0][4 * ks + g], b1 = flv[1][4 * ks + g];
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const real af = Al[(ks * MT + mt) * 64];
-        acc[0][mt] = M::mma(af, b0, acc[0][mt]);
-        acc[1][mt] = M::mma(af, b1, acc[1][mt]);
-      }
-    }
-  } else
-  for (int nt = tid >> 6; nt < NT; nt += kThreads / 64, ++ntl) {
-    const int col = nt * 16 + (lane & 15);
-    const bool cok = col < 9 * nE;
-    const int e = cok ? col / 9 : 0, k = cok ? col - 9 * (col / 9) : 0;
-    const real *qe = sq + e * 9 * Np;
-    const double *gm = smeta + e * DGW_META;
-    // input-side coefficients of this column, c[a][m] = s_m X^-1[a][x_m],
-    // with the material factor s_m and the metric column x_m of each of
-    // the three combined fields f_m given per component k by packed tables
-    // (branch-free: the sixteen lanes of a column tile hold different k):
-    //   k = 0..2 (vx, vy, vz):   f = sigma row k, s = 1/rho, x = (0, 1, 2)
-    //   k = 3..5 (sxx..szz):      f = (vx, vy, vz), s = lambda + 2 mu on
-    //                             x = k - 3, lambda elsewhere, x = (0, 1, 2)
-    //   k = 6 (syz): f = (vy, vz), s = mu, x = (2, 1)
-    //   k = 7 (sxz): f = (vx, vz), s = mu, x = (2, 0)
-    //   k = 8 (sxy): f = (vx, vy), s = mu, x = (1, 0)
-    // fields (4 bits per k, m = 0, 1, 2)
-    constexpr uint64_t F0 = 0x001000783ull, F1 = 0x122111648ull, F2 = 0x210222567ull;
-    // metric columns (2 bits per k) and material factor ids (3 bits per k:
-    // 0 1/rho, 1 lambda + 2 mu, 2 lambda, 3 mu, 4 zero)
-    constexpr uint32_t X0 = 0x1a000u, X1 = 0x01555u, X2 = 0x2aaaau;
-    constexpr uint32_t S0 = 0x36d2200u, S1 = 0x36d1400u, S2 = 0x490a400u;
-    int f0 = (int)((F0 >> (4 * k)) & 15), f1 = (int)((F1 >> (4 * k)) & 15),
-        f2 = (int)((F2 >> (4 * k)) & 15);
-    const real ri = (real)gm[M_RHOINV], la = (real)gm[M_LAM], mu = (real)gm[M_MU];
-    const real l2 = la + 2 * mu;
-    auto fac = [&](uint32_t S) -> real {
-      const int id = (int)((S >> (3 * k)) & 7);
-      return id == 0 ? ri : id == 1 ? l2 : id == 2 ? la : id == 3 ? mu : (real)0;
-    };
-    const real s0 = fac(S0), s1 = fac(S1), s2 = fac(S2);
-    const int x0 = (int)((X0 >> (2 * k)) & 3), x1 = (int)((X1 >> (2 * k)) & 3),
-              x2 = (int)((X2 >> (2 * k)) & 3);
-    real c[3][3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const real r0 = (real)gm[M_XINV + 3 * a], r1 = (real)gm[M_XINV + 3 * a + 1],
-                 r2 = (real)gm[M_XINV + 3 * a + 2];
-      auto pick = [&](int x) { return x == 0 ? r0 : x == 1 ? r1 : r2; };
-      c[a][0] = s0 * pick(x0);
-      c[a][1] = s1 * pick(x1);
-      c[a][2] = s2 * pick(x2);
-    }
-    if constexpr (AN) {
-      // anisotropic stress rows (k >= 3, Voigt row I = k - 3): the fields
-      // are (vx, vy, vz) and c[a][m] = sum_b C[I][voigt(m, b)] X^-1[a][b]
-      // (selects, so the column setup stays branch-free)
-      const bool st = k >= 3;
-      const int I = st ? k - 3 : 0;
-      const double *Cu = A.aniso + (k0 + e) * DGW_ANI + A_C;
-      real cr[6];
-#pragma unroll
-      for (int J = 0; J < 6; ++J) {
-        const int i = I < J ? I : J, j = I < J ? J : I;   // upper triangle
-        cr[J] = (real)Cu[i * (11 - i) / 2 + j];
-      }
-      constexpr int VG[3][3] = {{0, 5, 4}, {5, 1, 3}, {4, 3, 2}};   // voigt(m, b)
-#pragma unroll
-      for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-          real v = 0;
-#pragma unroll
-          for (int b = 0; b < 3; ++b) v += cr[VG[m][b]] * (real)gm[M_XINV + 3 * a + b];
-          c[a][m] = st ? v : c[a][m];
-        }
-      f0 = st ? 0 : f0;
-      f1 = st ? 1 : f1;
-      f2 = st ? 2 : f2;
-    }
-    const real *q0 = qe + f0 * Np, *q1 = qe + f1 * Np, *q2 = qe + f2 * Np;
-    v4 *ac = acc[ntl];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) ac[mt] = v4{0, 0, 0, 0};
     // volume: three reference directions, K = Np (padded to a multiple of 4)
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const real ca0 = c[a][0], ca1 = c[a][1], ca2 = c[a][2];
       const real *Ab = A.Avol + (size_t)a * KS * MT * 64 + lane + oz;
       for (int ks = 0; ks < KS; ++ks) {
         // rows past Np of the last k-step read a valid node and are zeroed
         // (a select, not a branch, so the direction stays one basic block)
         const int j = 4 * ks + g, jj = j < Np ? j : Np - 1;
-        real b = ca0 * q0[jj] + ca1 * q1[jj] + ca2 * q2[jj];
-        b = j < Np ? b : (real)0;
+        real b[HT];
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) ac[mt] = M::mma(Ab[(ks * MT + mt) * 64], b, ac[mt]);
+        for (int h = 0; h < HT; ++h) {
+          const real v = C[h].c[a][0] * qf[h][0][jj] + C[h].c[a][1] * qf[h][1][jj] +
+                         C[h].c[a][2] * qf[h][2][jj];
+          b[h] = j < Np ? v : (real)0;
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          const real af = Ab[(ks * MT + mt) * 64];
+#pragma unroll
+          for (int h = 0; h < HT; ++h) acc[h][mt] = M::mma(af, b[h], acc[h][mt]);
+        }
       }
     }
     // lift: the column's flux on the 4 Nfp face nodes
-    const real *fl = sfl + (e * 9 + k) * NF;
     const real *Al = A.Alift + lane + oz;
     for (int ks = 0; ks < KL; ++ks) {
-      const real b = fl[4 * ks + g];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) ac[mt] = M::mma(Al[(ks * MT + mt) * 64], b, ac[mt]);
+      for (int mt = 0; mt < MT; ++mt) {
+        const real af = Al[(ks * MT + mt) * 64];
+#pragma unroll
+        for (int h = 0; h < HT; ++h) acc[h][mt] = M::mma(af, fl[h][4 * ks + g], acc[h][mt]);
+      }
     }
   }
-  typename SP::vec rv[UV];
-#pragma unroll
-  for (int u = 0; u < UV; ++u) {
-    const int j = tid + u * kThreads;
-    if (!first && j < sp.nv) {
-      const typename SP::vec *rp = (const typename SP::vec *)(rs + sp.hd) + j;
-      if constexpr (kStream)
-        rv[u] = __builtin_nontemporal_load(rp);
-      else
-        rv[u] = *rp;
-    }
-    else rv[u] = typename SP::vec{};
-  }
-  const int tl0 = sp.hd + SP::VW * sp.nv;
-  const real rh = (!first && tid < sp.hd) ? rs[tid] : (real)0;
-  const real rt = (!first && tid < sp.tl) ? rs[tl0 + tid] : (real)0;
+  Update<N, real, BE> U(A, k0, shot, nE, qout, res, tid);
   __syncthreads();   // every wave is done with the flux buffer
   // right-hand side to LDS in the block's (element, field, node) order
-  ntl = 0;
-  for (int nt = tid >> 6; nt < NT; nt += kThreads / 64, ++ntl) {
-    const int col = nt * 16 + (lane & 15);
-    if (col < 9 * nE) {
+  if (w < NT) {
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+    for (int h = 0; h < HT; ++h) {
+      const int col = (w + h * NW) * 16 + (lane & 15);
+      if (col < 9 * nE) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = 16 * mt + M::row(g, r);
-          if (i < Np) sfl[col * Np + i] = acc[ntl][mt][r];
-        }
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int i = 16 * mt + M::row(g, r);
+            if (i < Np) sfl[col * Np + i] = acc[h][mt][r];
+          }
+      }
     }
   }
   __syncthreads();
-  // point source and LSERK update over the contiguous span
-  const real ra = (real)A.rk_a, rb = (real)A.rk_b, rdt = (real)A.dt;
-  const int64_t es = (int64_t)A.src_elem[shot] - k0;   // source element in block
-  double s = 0.0;
-  const double *spar = A.src_par + 10 * shot;
-  if (es >= 0 && es < nE) s = ricker_d(((double)step + A.rk_c) * A.dt, spar[6], spar[7], spar[8]);
-  auto update = [&](int t, real rold) -> real2v<real> {
-    real rhs = sfl[t];
-    const int e = t / (9 * Np), ci = t - e * 9 * Np, c = ci / Np, i = ci - c * Np;
-    if (e == es && c >= 3) rhs += (real)(s * spar[c - 3] * A.src_vec[shot * Np + i]);
-    if (A.sponge) rhs -= (real)ssig[e] * sq[t];
-    const real rn = first ? rdt * rhs : ra * rold + rdt * rhs;
-    return {rn, sq[t] + rb * rn};
-  };
+  U.apply(A, sq, sfl, ssig, nE, k0, shot, step, tid);
+}
+
+// The transform over the Klein four-group (sym.h), its own inverse up to 4.
+template <typename real>
+__device__ __forceinline__ void sym4(const real (&a)[4], real (&t)[4]) {
+  const real s = a[0] + a[1], d = a[0] - a[1], u = a[2] + a[3], v = a[2] - a[3];
+  t[0] = s + u;
+  t[1] = s - u;
+  t[2] = d + v;
+  t[3] = d - v;
+}
+
+// Phase 3 on the matrix cores, FP64 from order 4: the same GEMM in the symmetry
+// components of the lattice (sym.h).  With cs_p the sum of the two
+// coefficients c_a, a != p, component x of a column's right-hand side is
+//   r_x(o') = sum_p A_{x,p}[o'][.] (sum_m cs_p[m] q^_{m, x xor p}(.))
+//             + B_x[o'][.] F^_x(.),
+// the factor -1/8 in A and 1/4 in B.  A lane that supplies row 4 ks + g of an
+// operand reads the four nodes of that orbit from the LDS tile and transforms
+// them in registers, which serves all twelve blocks of the k-step; the flux
+// is stored with its four face images side by side, so the lift's operand is
+// one transform of four neighbours.  Rows are orbits, and the accumulators of
+// the four components hold the same orbits in the same lane and register, so
+// the result is transformed back in registers too.
+//
+// The GEMM phase was bound by its operator loads and matrix instructions: the
+// nodal form needs 126 of each per 16 columns at order 4 (3 row tiles x 42
+// k-steps), this one 49; order 5: 252 -> 72, order 6: 546 -> 194.  Measured
+// (FP64 stage launch, nodal form -> this): order 4, 82944 elements, 348 -> 268
+// us, anisotropic 462 -> 362 us; order 5, 24576 elements, 211 -> 137 us; order
+// 6, 24576 elements, 776 -> 282 us.  Order 3 keeps the nodal form: 50 -> 36
+// fragments only (five of sixteen rows used), 54.1 against 57.8 us; orders 1
+// and 2 have fewer fragments in the nodal form.
+template <int N, typename real, int BE, bool AN>
+__device__ __forceinline__ void phase3_sym(const StageArgs<real> &A, const real *sq,
+                                           real *sfl, const double *smeta,
+                                           const double *ssig, int nE, int64_t k0,
+                                           int shot, int64_t step, real *qout, real *res,
+                                           const uint32_t (&nodes)[Sym<N>::KS], int oz,
+                                           int tid) {
+  using S = Sym<N>;
+  using M = Mma<real>;
+  using v4 = typename M::v4;
+  constexpr int Np = S::Np, Nfp = S::Nfp, NF = 4 * Nfp, MT = S::MT, KS = S::KS;
+  constexpr int NT = (9 * BE + 15) / 16;      // column tiles
+  constexpr int NW = kThreads / 64;
+  constexpr int HT = (NT + NW - 1) / NW;      // column tiles per wave
+  static_assert(Np <= NF, "the flux buffer holds the right-hand side");
+  const int lane = tid & 63, g = lane >> 4, w = tid >> 6;
+  v4 acc[HT][4][MT];
+  if (w < NT) {
+    const real *qf[HT][3], *fl[HT];
+    real cs[HT][4][3];
 #pragma unroll
-  for (int u = 0; u < UV; ++u) {
-    const int j = tid + u * kThreads;
-    if (j >= sp.nv) continue;
-    const int b = sp.hd + SP::VW * j;
-    typename SP::vec nr, nq;
+    for (int h = 0; h < HT; ++h) {
+      const int col = (w + h * NW) * 16 + (lane & 15);
+      const bool cok = col < 9 * nE;
+      const int e = cok ? col / 9 : 0, k = cok ? col - 9 * (col / 9) : 0;
+      Column<real> C;
+      column_setup<real, AN>(A, smeta + e * DGW_META, k0 + e, k, C);
 #pragma unroll
-    for (int l = 0; l < SP::VW; ++l) {
-      const real2v<real> o = update(b + l, rv[u][l]);
-      nr[l] = o.r;
-      nq[l] = o.q;
+      for (int m = 0; m < 3; ++m) {
+        qf[h][m] = sq + (e * 9 + C.f[m]) * Np;
+        cs[h][1][m] = C.c[1][m] + C.c[2][m];
+        cs[h][2][m] = C.c[0][m] + C.c[2][m];
+        cs[h][3][m] = C.c[0][m] + C.c[1][m];
+      }
+      fl[h] = sfl + (e * 9 + k) * NF;
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[h][x][mt] = v4{0, 0, 0, 0};
     }
-    if constexpr (kStream) {
-      __builtin_nontemporal_store(nr, (typename SP::vec *)(rs + b));
-      if constexpr (sizeof(real) == 8)
-        __builtin_nontemporal_store(nq, (typename SP::vec *)(qo + b));
-      else
-        *(typename SP::vec *)(qo + b) = nq;
-    } else {
-      *(typename SP::vec *)(rs + b) = nr;
-      *(typename SP::vec *)(qo + b) = nq;
+    const real *Ab = A.Asym + lane + oz;
+    int fr = 0;   // a constant at every use once unrolled
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      real qt[HT][3][4];
+#pragma unroll
+      for (int h = 0; h < HT; ++h)
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+          real v[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) v[j] = qf[h][m][(nodes[ks] >> (8 * j)) & 255];
+          sym4(v, qt[h][m]);
+        }
+#pragma unroll
+      for (int p = 1; p < 4; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (!S::kstep(ks, i)) continue;
+          real y[HT];
+#pragma unroll
+          for (int h = 0; h < HT; ++h)
+            y[h] = cs[h][p][0] * qt[h][0][i] + cs[h][p][1] * qt[h][1][i] +
+                   cs[h][p][2] * qt[h][2][i];
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt, ++fr) {
+            const real af = Ab[fr * 64];
+#pragma unroll
+            for (int h = 0; h < HT; ++h)
+              acc[h][i ^ p][mt] = M::mma(af, y[h], acc[h][i ^ p][mt]);
+          }
+        }
+    }
+#pragma unroll
+    for (int ks = 0; ks < S::KF; ++ks) {
+      // the rows past Nfp of the last k-step read a valid node; their
+      // operator entries are zero
+      const int j = 4 * ks + g, jj = j < Nfp ? j : Nfp - 1;
+      real ft[HT][4];
+#pragma unroll
+      for (int h = 0; h < HT; ++h) {
+        real v[4];
+#pragma unroll
+        for (int f = 0; f < 4; ++f) v[f] = fl[h][4 * jj + f];
+        sym4(v, ft[h]);
+      }
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt, ++fr) {
+          const real af = Ab[fr * 64];
+#pragma unroll
+          for (int h = 0; h < HT; ++h) acc[h][x][mt] = M::mma(af, ft[h][x], acc[h][x][mt]);
+        }
     }
   }
-  if (tid < sp.hd) {
-    const real2v<real> o = update(tid, rh);
-    if constexpr (kStream)
-      __builtin_nontemporal_store(o.r, rs + tid);
-    else
-      rs[tid] = o.r;
-    qo[tid] = o.q;
+  Update<N, real, BE> U(A, k0, shot, nE, qout, res, tid);
+  __syncthreads();   // every wave is done with the flux buffer
+  // right-hand side to LDS in the block's (element, field, node) order;
+  // register r of this lane holds orbit 16 mt + 4 r + g
+  if (w < NT) {
+#pragma unroll
+    for (int h = 0; h < HT; ++h) {
+      const int col = (w + h * NW) * 16 + (lane & 15);
+      if (col < 9 * nE) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const real a[4] = {acc[h][0][ks / 4][ks % 4], acc[h][1][ks / 4][ks % 4],
+                             acc[h][2][ks / 4][ks % 4], acc[h][3][ks / 4][ks % 4]};
+          real t[4];
+          sym4(a, t);
+          if (4 * ks + g < S::nO)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              sfl[col * Np + ((nodes[ks] >> (8 * j)) & 255)] = t[j];
+        }
+      }
+    }
   }
-  if (tid < sp.tl) {
-    const real2v<real> o = update(tl0 + tid, rt);
-    if constexpr (kStream)
-      __builtin_nontemporal_store(o.r, rs + tl0 + tid);
-    else
-      rs[tl0 + tid] = o.r;
-    qo[tl0 + tid] = o.q;
-  }
+  __syncthreads();
+  U.apply(A, sq, sfl, ssig, nE, k0, shot, step, tid);
 }
 
 // Phase 3 on the vector ALUs: one thread per (element, node).  AN:
@@ -529,7 +670,8 @@ struct FaceTab {
   static constexpr int FI = (BE * 4 * Sz<N>::Nfp + kThreads - 1) / kThreads;
   int cn[FI];
   int64_t gb[FI];
-  int n1[FI];   // the face node's volume node in its own element
+  int n1[FI];   // the face node's volume node in its own element, and its
+                // slot in the matrix-core form's flux row << 16
 };
 
 template <int N, typename real, int BE>
@@ -550,7 +692,7 @@ __device__ __forceinline__ void face_tables(const StageArgs<real> &A, int64_t it
     const int cn = A.conn[k * 4 + f];
     const int nb = A.nbnode[k * NF + fm];
     T.cn[u] = ok ? cn : CONN_ABSORB;
-    T.n1[u] = A.fmask[fm];
+    T.n1[u] = A.fslot[fm];
     // masked arithmetic rather than a select, so the compiler keeps the
     // node-table load unconditional (not behind a wait for cn)
     const int64_t live = -(int64_t)(ok && cn >= 0);
@@ -643,6 +785,14 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
   int oz;
   asm volatile("v_mov_b32 %0, 0" : "=v"(oz));
 
+  // the nodes of this lane's orbits (sym.h), four to a word
+  constexpr bool kSym = (V == 1 || V == 3) && kSymForm<N, real>;
+  uint32_t nodes[Sym<N>::KS];
+  if constexpr (kSym)
+#pragma unroll
+    for (int ks = 0; ks < Sym<N>::KS; ++ks)
+      nodes[ks] = A.symnode[4 * ks + ((tid & 63) >> 4)];
+
   // ---- 1. all global reads of the item's fields are in flight together ----
   // neighbour traces of this thread's face nodes go to registers; read
   // unconditionally (boundary and idle face items have offset 0, an
@@ -691,7 +841,7 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
     const int e = t / NF, fm = t - e * NF, f = fm / Nfp;
     const double *g = smeta + e * DGW_META;
     const real *qe = sq + e * 9 * Np;
-    const int n1 = T.n1[u];
+    const int n1 = T.n1[u] & 0xffff;
     real qm[9], p[9];
 #pragma unroll
     for (int c = 0; c < 9; ++c) qm[c] = qe[c * Np + n1];
@@ -778,7 +928,7 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
     } else {
       // all nine lifted components, field-major (the GEMM's data side)
       const real Dvx = fs * ux, Dvy = fs * uy, Dvz = fs * uz;
-      real *d = sfl + e * 9 * NF + fm;
+      real *d = sfl + e * 9 * NF + (kSymForm<N, real> ? T.n1[u] >> 16 : fm);
       d[0 * NF] = fs * wx * ri;
       d[1 * NF] = fs * wy * ri;
       d[2 * NF] = fs * wz * ri;
@@ -815,7 +965,10 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
   __syncthreads();
 
 
-  if constexpr (V == 1 || V == 3)
+  if constexpr (kSym)
+    phase3_sym<N, real, BE, V == 3>(A, sq, sfl, smeta, ssig, nE, k0, shot, step, qout, res,
+                                    nodes, oz, tid);
+  else if constexpr (V == 1 || V == 3)
     phase3_mfma<N, real, BE, V == 3>(A, sq, sfl, smeta, ssig, nE, k0, shot, step, qout, res,
                                      oz, tid);
   else
@@ -894,7 +1047,8 @@ hipError_t launch_t(int be, int wpc, int ncu, int nshots, const StageArgs<real> 
                     hipStream_t st) {
   constexpr int A_ = Shapes<N, real, V>::a, B_ = Shapes<N, real, V>::b;
   if (be != A_ && be != B_) return hipErrorInvalidValue;
-  if ((V == 1 || V == 3) && (a.Avol == nullptr || a.Alift == nullptr))
+  if ((V == 1 || V == 3) && (kSymForm<N, real> ? a.Asym == nullptr || a.symnode == nullptr
+                                    : a.Avol == nullptr || a.Alift == nullptr))
     return hipErrorInvalidValue;
   const int64_t nblk = (a.K + be - 1) / be;
   const int64_t total = nblk * nshots;
