@@ -135,58 +135,65 @@ static std::vector<real> transpose(const std::vector<double> &A, int rows,
   return T;
 }
 
-// Operator fragments of the matrix-core stage kernel in the symmetry
-// components of the lattice (sym.h), in the kernel's order, and the node and
-// slot tables.  Tile row i of a fragment is orbit 16 mt + i: register r of
-// lane group g of an FP64 accumulator then holds orbit 16 mt + 4 r + g.
+// Operator fragments of the FP64 matrix-core stage kernel in the symmetry
+// components of the lattice (sym.h), in the kernel's order: pairs of fragments,
+// entry [pair][4 k + i][fragment] with i the row and k the product of a 4x4
+// block; the nodes of each orbit; and the order of the face nodes.
 template <int N>
 static void sym_tables(const RefElem &R, std::vector<double> &frag,
-                       std::vector<uint32_t> &nodes, std::vector<int32_t> &fslot) {
+                       std::vector<uint32_t> &nodes, std::vector<int32_t> &order) {
   using S = Sym<N>;
   constexpr int Np = S::Np, Nfp = S::Nfp, NF = 4 * Nfp;
-  frag.assign((size_t)S::frags() * 64, 0.0);
-  double *fp = frag.data();
-  auto orbit_row = [](int mt, int l) { return 16 * mt + l % 16; };
-  for (int ks = 0; ks < S::KS; ++ks)
+  frag.assign((size_t)S::frags * 16, 0.0);
+  int fr = 0;
+  auto put = [&](int k, int i, long double v) {
+    frag[(size_t)(fr / 2) * 32 + 2 * (4 * k + i) + fr % 2] = (double)v;
+  };
+  for (int ks = S::KS - 1; ks >= 0; --ks) {
+    fr = S::layout.at[S::KS - 1 - ks];
     for (int p = 1; p < 4; ++p)
-      for (int i = 0; i < 4; ++i) {
-        if (!S::kstep(ks, i)) continue;
-        for (int mt = 0; mt < S::MT; ++mt, fp += 64)
-          for (int l = 0; l < 64; ++l) {
-            const int ro = orbit_row(mt, l), co = 4 * ks + l / 16;
-            if (!S::has(ro, i ^ p) || !S::has(co, i)) continue;
-            const int row = S::tab.at[ro][0] * Np;
-            long double v = 0;
-            for (int j = 0; j < 4; ++j) {
-              const int n = S::tab.at[co][j];
-              bool seen = false;   // short orbits repeat their nodes
-              for (int j2 = 0; j2 < j; ++j2) seen = seen || S::tab.at[co][j2] == n;
-              if (seen) continue;
-              const long double t = (long double)sym_sign(p, 1) * R.Dr[row + n] +
-                                    (long double)sym_sign(p, 2) * R.Ds[row + n] +
-                                    (long double)sym_sign(p, 3) * R.Dt[row + n];
-              v += sym_sign(i, j) * t;
+      for (int c = 0; c < 4; ++c) {
+        if (ks >= S::steps(c)) continue;
+        for (int r = 0; r < S::steps(c ^ p); ++r, ++fr)
+          for (int k = 0; k < 4; ++k)
+            for (int i = 0; i < 4; ++i) {
+              const int ro = S::orbit(c ^ p, 4 * r + i), co = S::orbit(c, 4 * ks + k);
+              if (ro < 0 || co < 0) continue;
+              const int row = S::tab.at[ro][0] * Np;
+              long double v = 0;
+              for (int j = 0; j < 4; ++j) {
+                const int n = S::tab.at[co][j];
+                bool seen = false;   // short orbits repeat their nodes
+                for (int j2 = 0; j2 < j; ++j2) seen = seen || S::tab.at[co][j2] == n;
+                if (seen) continue;
+                const long double t = (long double)sym_sign(p, 1) * R.Dr[row + n] +
+                                      (long double)sym_sign(p, 2) * R.Ds[row + n] +
+                                      (long double)sym_sign(p, 3) * R.Dt[row + n];
+                v += sym_sign(c, j) * t;
+              }
+              put(k, i, -v / 8);
             }
-            fp[l] = (double)(-v / 8);
-          }
       }
-  for (int ks = 0; ks < S::KF; ++ks)
-    for (int i = 0; i < 4; ++i)
-      for (int mt = 0; mt < S::MT; ++mt, fp += 64)
-        for (int l = 0; l < 64; ++l) {
-          const int ro = orbit_row(mt, l), j = 4 * ks + l / 16;
-          if (!S::has(ro, i) || j >= Nfp) continue;
-          long double v = 0;
-          for (int g = 0; g < 4; ++g)
-            v += sym_sign(i, g) * (long double)R.LIFT[(size_t)S::tab.at[ro][g] * NF + j];
-          fp[l] = (double)(v / 4);
-        }
+  }
+  for (int ks = 0; ks < S::KF; ++ks) {
+    fr = S::layout.at[S::KS + ks];
+    for (int c = 0; c < 4; ++c)
+      for (int r = 0; r < S::steps(c); ++r, ++fr)
+        for (int k = 0; k < 4; ++k)
+          for (int i = 0; i < 4; ++i) {
+            const int ro = S::orbit(c, 4 * r + i), j = 4 * ks + k;
+            if (ro < 0 || j >= Nfp) continue;
+            long double v = 0;
+            for (int g = 0; g < 4; ++g)
+              v += sym_sign(c, g) * (long double)R.LIFT[(size_t)S::tab.at[ro][g] * NF + j];
+            put(k, i, v / 4);
+          }
+  }
   nodes.assign(4 * S::KS, 0);
   for (int o = 0; o < 4 * S::KS; ++o)
     for (int j = 0; j < 4; ++j)
       nodes[o] |= (uint32_t)S::tab.at[o < S::nO ? o : 0][j] << (8 * j);
-  fslot.resize(NF);
-  for (int t = 0; t < NF; ++t) fslot[t] = R.fmask[t] | (int32_t)S::tab.slot[t] << 16;
+  order.assign(S::tab.face, S::tab.face + NF);
 }
 
 int dgw_ctx::upload_operators() {
@@ -270,28 +277,33 @@ int dgw_ctx::upload_operators() {
       if ((rc = upload(d_Alf, aff.data(), rs * aff.size()))) return rc;
     }
   }
-  {
+  if (precision == 64) {
     std::vector<double> fr;
     std::vector<uint32_t> nd;
-    std::vector<int32_t> fs;
+    std::vector<int32_t> order;
     switch (R.N) {
-      case 1: sym_tables<1>(R, fr, nd, fs); break;
-      case 2: sym_tables<2>(R, fr, nd, fs); break;
-      case 3: sym_tables<3>(R, fr, nd, fs); break;
-      case 4: sym_tables<4>(R, fr, nd, fs); break;
-      case 5: sym_tables<5>(R, fr, nd, fs); break;
-      default: sym_tables<6>(R, fr, nd, fs); break;
+      case 1: sym_tables<1>(R, fr, nd, order); break;
+      case 2: sym_tables<2>(R, fr, nd, order); break;
+      case 3: sym_tables<3>(R, fr, nd, order); break;
+      case 4: sym_tables<4>(R, fr, nd, order); break;
+      case 5: sym_tables<5>(R, fr, nd, order); break;
+      default: sym_tables<6>(R, fr, nd, order); break;
     }
+    std::vector<int32_t> fs(NF);
+    std::vector<uint8_t> nb((size_t)mesh.K * NF);
+    for (int t = 0; t < NF; ++t) fs[t] = R.fmask[order[t]];
+    for (int64_t k = 0; k < mesh.K; ++k)
+      for (int t = 0; t < NF; ++t) nb[k * NF + t] = mesh.nbnode[k * NF + order[t]];
+    d_Asym = dalloc(sizeof(double) * fr.size());
     d_symnode = (uint32_t *)dalloc(sizeof(uint32_t) * nd.size());
-    d_fslot = (int32_t *)dalloc(sizeof(int32_t) * fs.size());
-    if (!d_symnode || !d_fslot) return fail(DGW_ENOMEM, "device allocation failed (operators)");
-    if (precision == 64) {
-      d_Asym = dalloc(sizeof(double) * fr.size());
-      if (!d_Asym) return fail(DGW_ENOMEM, "device allocation failed (operators)");
-      if ((rc = upload(d_Asym, fr.data(), sizeof(double) * fr.size()))) return rc;
-    }
+    d_fsym = (int32_t *)dalloc(sizeof(int32_t) * NF);
+    d_nbsym = (uint8_t *)dalloc(nb.size());
+    if (!d_Asym || !d_symnode || !d_fsym || !d_nbsym)
+      return fail(DGW_ENOMEM, "device allocation failed (operators)");
+    if ((rc = upload(d_Asym, fr.data(), sizeof(double) * fr.size()))) return rc;
     if ((rc = upload(d_symnode, nd.data(), sizeof(uint32_t) * nd.size()))) return rc;
-    if ((rc = upload(d_fslot, fs.data(), sizeof(int32_t) * fs.size()))) return rc;
+    if ((rc = upload(d_fsym, fs.data(), sizeof(int32_t) * NF))) return rc;
+    if ((rc = upload(d_nbsym, nb.data(), nb.size()))) return rc;
   }
   std::vector<int32_t> fm(R.fmask.begin(), R.fmask.end());
   if ((rc = upload(d_fmask, fm.data(), sizeof(int32_t) * fm.size()))) return rc;

@@ -68,7 +68,8 @@ struct dgw_ctx {
   void *d_Alf = nullptr;                         // per-face lift fragments
   void *d_Asym = nullptr;                        // symmetry-component fragments (sym.h)
   uint32_t *d_symnode = nullptr;
-  int32_t *d_fslot = nullptr;
+  int32_t *d_fsym = nullptr;
+  uint8_t *d_nbsym = nullptr;
   double *d_M = nullptr;
   void *d_q[2] = {nullptr, nullptr};
   void *d_res = nullptr;
@@ -191,7 +192,8 @@ inline void stage_args(const dgw_ctx *c, dgw::StageArgs<real> &a, const void *in
   a.Alf = (const real *)c->d_Alf;
   a.Asym = (const real *)c->d_Asym;
   a.symnode = c->d_symnode;
-  a.fslot = c->d_fslot;
+  a.fsym = c->d_fsym;
+  a.nbsym = c->d_nbsym;
   a.fmask = c->d_fmask;
   a.K = c->mesh.K;
   a.shot_stride = c->mesh.K * 9 * c->R.Np;

@@ -90,9 +90,9 @@ struct StageArgs {
   const uint8_t *nbnode;        // [K][4 Nfp] neighbour volume node per face node
   const real *DrT, *DsT, *DtT;  // [j][i] (transposed)
   const real *LIFTT;            // [4Nfp][Np] (transposed)
-  // operator fragments of the FP64 matrix-core form at orders 4-6 in MFMA lane
-  // order, in the lattice's symmetry components (sym.h), and the nodes of
-  // orbit o, [o] = four bytes
+  // operator fragments of the FP64 matrix-core form from order 3, in the
+  // lattice's symmetry components (sym.h), and the nodes of orbit o, [o] = four
+  // bytes (FP64 contexts only, as nbsym and fsym)
   const real *Asym;
   const uint32_t *symnode;
   // nodal operator fragments in MFMA lane order (the other forms):
@@ -103,9 +103,10 @@ struct StageArgs {
   // Alf[f][ks][mt][64] = c_f LIFT[16 mt + l % 16][f Nfp + 4 ks + l / 16] for
   // 4 ks + l / 16 < Nfp, else 0; c_0 = 2, c_1 = c_2 = c_3 = -2
   const real *Alf;
-  // [4 Nfp] volume node of each face node, and its slot 4 j + f in a flux
-  // row of the matrix-core form (sym.h) << 16
-  const int32_t *fslot;
+  // nbnode and fmask with each face's nodes in the order of their face-0
+  // preimages (sym.h)
+  const uint8_t *nbsym;
+  const int32_t *fsym;
   const int32_t *fmask;         // [4 Nfp]
   int64_t K;
   int64_t shot_stride;          // K * 9 * Np

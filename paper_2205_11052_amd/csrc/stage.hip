@@ -20,18 +20,22 @@
 //   2. one thread per (element, face node): exact Riemann flux in jump form
 //      (optionally blended with the central flux; for anisotropic elements
 //      from the face's impedance matrices) from the own trace (LDS) and the
-//      neighbour's (registers); six lifted
-//      quantities go to LDS: the velocity flux and the velocity change dv,
-//      both times Fscale (the stress flux is lambda (n.dv) I + mu (dv n^T +
-//      n dv^T), n constant per face, so it is formed after lifting dv);
-//   3. one thread per (element, node): reference derivatives of the nine
-//      fields with Dr, Ds, Dt, the physical volume terms, + the lifted flux,
-//      + point source, then res = a res + dt rhs and q_out = q_in + b res.
+//      neighbour's (registers); six quantities go to LDS, the velocity flux
+//      and the velocity change dv (the stress flux is lambda (n.dv) I +
+//      mu (dv n^T + n dv^T), n constant per face, so it is formed from the
+//      lifted dv or on the way into the lift), or all nine components;
+//   3. the volume terms and the lifted flux, by one of three forms: one thread
+//      per (element, node) on the vector ALUs (phase3_nodes); a GEMM on the
+//      matrix cores in nodal form (phase3_mfma: FP32, and FP64 at orders 1 and
+//      2); a GEMM in the symmetry components of the lattice (SymGemm: FP64
+//      from order 3).  Then + point source, res = a res + dt rhs and
+//      q_out = q_in + b res.
 // q_in and q_out are distinct buffers (neighbour traces are read from q_in
 // while other blocks write q_out); res is element-local and updated in place.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "dgw_internal.h"
 #include "stage_common.h"
@@ -42,11 +46,11 @@ namespace dgw {
 namespace {
 
 constexpr int kThreads = 256;
-// Whether the matrix-core form of an order and precision works in symmetry
-// components (phase3_sym): FP64 from order 4.  FP32 keeps the nodal form's
-// order of summation, and with it its results to the last bit.
+// Whether the matrix-core form of a precision works in symmetry components
+// (SymGemm): FP64.  FP32 keeps the nodal form's order of summation, and with
+// it its results to the last bit.
 template <int N, typename real>
-constexpr bool kSymForm = N >= 4 && sizeof(real) == 8;
+constexpr bool kSymForm = N >= 3 && sizeof(real) == 8;
 using namespace stagec;
 
 // Residual and update of a block's contiguous span by 16-byte vectors; the
@@ -66,7 +70,7 @@ struct Update {
   static constexpr bool kStream = N >= 4;
   using SP = Span16<real>;
   static constexpr int UV = (BE * 9 * Np / SP::VW + kThreads - 1) / kThreads;
-  SP sp;
+  SP sp{0, 0};
   bool first;
   real *rs, *qo;
   int tl0;
@@ -74,9 +78,9 @@ struct Update {
   real rh, rt;
 
   // residual loads of this thread's update items, all issued together
-  __device__ __forceinline__ Update(const StageArgs<real> &A, int64_t k0, int shot, int nE,
-                                    real *qout, real *res, int tid)
-      : sp(shot * A.shot_stride + k0 * 9 * Np, nE * 9 * Np) {
+  __device__ __forceinline__ void load(const StageArgs<real> &A, int64_t k0, int shot, int nE,
+                                       real *qout, real *res, int tid) {
+    sp = SP(shot * A.shot_stride + k0 * 9 * Np, nE * 9 * Np);
     first = A.rk_a == 0.0;
     rs = res + k0 * 9 * Np;
     qo = qout + k0 * 9 * Np;
@@ -97,21 +101,35 @@ struct Update {
     rt = (!first && tid < sp.tl) ? rs[tl0 + tid] : (real)0;
   }
 
-  // point source and LSERK update over the contiguous span
+  // LSERK update over the contiguous span, with the point source (element
+  // es of the block) and the sponge where the block has them: a plain block
+  // needs no element and node of each value, whose divisions were a third of
+  // the update's instructions
   __device__ __forceinline__ void apply(const StageArgs<real> &A, const real *sq,
                                         const real *sfl, const double *ssig, int nE,
-                                        int64_t k0, int shot, int64_t step, int tid) {
+                                        int64_t es, int shot, int64_t step, int tid) {
+    if ((es >= 0 && es < nE) || A.sponge)
+      sweep<true>(A, sq, sfl, ssig, nE, es, shot, step, tid);
+    else
+      sweep<false>(A, sq, sfl, ssig, nE, es, shot, step, tid);
+  }
+
+  template <bool EXTRA>
+  __device__ __forceinline__ void sweep(const StageArgs<real> &A, const real *sq,
+                                        const real *sfl, const double *ssig, int nE,
+                                        int64_t es, int shot, int64_t step, int tid) {
     const real ra = (real)A.rk_a, rb = (real)A.rk_b, rdt = (real)A.dt;
-    const int64_t es = (int64_t)A.src_elem[shot] - k0;   // source element in block
     double s = 0.0;
     const double *spar = A.src_par + 10 * shot;
-    if (es >= 0 && es < nE)
+    if (EXTRA && es >= 0 && es < nE)
       s = ricker_d(((double)step + A.rk_c) * A.dt, spar[6], spar[7], spar[8]);
     auto update = [&](int t, real rold) -> real2v<real> {
       real rhs = sfl[t];
-      const int e = t / (9 * Np), ci = t - e * 9 * Np, c = ci / Np, i = ci - c * Np;
-      if (e == es && c >= 3) rhs += (real)(s * spar[c - 3] * A.src_vec[shot * Np + i]);
-      if (A.sponge) rhs -= (real)ssig[e] * sq[t];
+      if constexpr (EXTRA) {
+        const int e = t / (9 * Np), ci = t - e * 9 * Np, c = ci / Np, i = ci - c * Np;
+        if (e == es && c >= 3) rhs += (real)(s * spar[c - 3] * A.src_vec[shot * Np + i]);
+        if (A.sponge) rhs -= (real)ssig[e] * sq[t];
+      }
       const real rn = first ? rdt * rhs : ra * rold + rdt * rhs;
       return {rn, sq[t] + rb * rn};
     };
@@ -256,7 +274,7 @@ __device__ __forceinline__ void phase3_mfma(const StageArgs<real> &A, const real
                                             real *sfl, const double *smeta,
                                             const double *ssig, int nE,
                                             int64_t k0, int shot, int64_t step,
-                                            real *qout, real *res, int oz, int tid) {
+                                            int64_t src, real *qout, real *res, int oz, int tid) {
   using M = Mma<real>;
   using v4 = typename M::v4;
   constexpr int Np = Sz<N>::Np, NF = 4 * Sz<N>::Nfp;
@@ -318,7 +336,8 @@ __device__ __forceinline__ void phase3_mfma(const StageArgs<real> &A, const real
       }
     }
   }
-  Update<N, real, BE> U(A, k0, shot, nE, qout, res, tid);
+  Update<N, real, BE> U;
+  U.load(A, k0, shot, nE, qout, res, tid);
   __syncthreads();   // every wave is done with the flux buffer
   // right-hand side to LDS in the block's (element, field, node) order
   if (w < NT) {
@@ -337,161 +356,7 @@ __device__ __forceinline__ void phase3_mfma(const StageArgs<real> &A, const real
     }
   }
   __syncthreads();
-  U.apply(A, sq, sfl, ssig, nE, k0, shot, step, tid);
-}
-
-// The transform over the Klein four-group (sym.h), its own inverse up to 4.
-template <typename real>
-__device__ __forceinline__ void sym4(const real (&a)[4], real (&t)[4]) {
-  const real s = a[0] + a[1], d = a[0] - a[1], u = a[2] + a[3], v = a[2] - a[3];
-  t[0] = s + u;
-  t[1] = s - u;
-  t[2] = d + v;
-  t[3] = d - v;
-}
-
-// Phase 3 on the matrix cores, FP64 from order 4: the same GEMM in the symmetry
-// components of the lattice (sym.h).  With cs_p the sum of the two
-// coefficients c_a, a != p, component x of a column's right-hand side is
-//   r_x(o') = sum_p A_{x,p}[o'][.] (sum_m cs_p[m] q^_{m, x xor p}(.))
-//             + B_x[o'][.] F^_x(.),
-// the factor -1/8 in A and 1/4 in B.  A lane that supplies row 4 ks + g of an
-// operand reads the four nodes of that orbit from the LDS tile and transforms
-// them in registers, which serves all twelve blocks of the k-step; the flux
-// is stored with its four face images side by side, so the lift's operand is
-// one transform of four neighbours.  Rows are orbits, and the accumulators of
-// the four components hold the same orbits in the same lane and register, so
-// the result is transformed back in registers too.
-//
-// The GEMM phase was bound by its operator loads and matrix instructions: the
-// nodal form needs 126 of each per 16 columns at order 4 (3 row tiles x 42
-// k-steps), this one 49; order 5: 252 -> 72, order 6: 546 -> 194.  Measured
-// (FP64 stage launch, nodal form -> this): order 4, 82944 elements, 348 -> 268
-// us, anisotropic 462 -> 362 us; order 5, 24576 elements, 211 -> 137 us; order
-// 6, 24576 elements, 776 -> 282 us.  Order 3 keeps the nodal form: 50 -> 36
-// fragments only (five of sixteen rows used), 54.1 against 57.8 us; orders 1
-// and 2 have fewer fragments in the nodal form.
-template <int N, typename real, int BE, bool AN>
-__device__ __forceinline__ void phase3_sym(const StageArgs<real> &A, const real *sq,
-                                           real *sfl, const double *smeta,
-                                           const double *ssig, int nE, int64_t k0,
-                                           int shot, int64_t step, real *qout, real *res,
-                                           const uint32_t (&nodes)[Sym<N>::KS], int oz,
-                                           int tid) {
-  using S = Sym<N>;
-  using M = Mma<real>;
-  using v4 = typename M::v4;
-  constexpr int Np = S::Np, Nfp = S::Nfp, NF = 4 * Nfp, MT = S::MT, KS = S::KS;
-  constexpr int NT = (9 * BE + 15) / 16;      // column tiles
-  constexpr int NW = kThreads / 64;
-  constexpr int HT = (NT + NW - 1) / NW;      // column tiles per wave
-  static_assert(Np <= NF, "the flux buffer holds the right-hand side");
-  const int lane = tid & 63, g = lane >> 4, w = tid >> 6;
-  v4 acc[HT][4][MT];
-  if (w < NT) {
-    const real *qf[HT][3], *fl[HT];
-    real cs[HT][4][3];
-#pragma unroll
-    for (int h = 0; h < HT; ++h) {
-      const int col = (w + h * NW) * 16 + (lane & 15);
-      const bool cok = col < 9 * nE;
-      const int e = cok ? col / 9 : 0, k = cok ? col - 9 * (col / 9) : 0;
-      Column<real> C;
-      column_setup<real, AN>(A, smeta + e * DGW_META, k0 + e, k, C);
-#pragma unroll
-      for (int m = 0; m < 3; ++m) {
-        qf[h][m] = sq + (e * 9 + C.f[m]) * Np;
-        cs[h][1][m] = C.c[1][m] + C.c[2][m];
-        cs[h][2][m] = C.c[0][m] + C.c[2][m];
-        cs[h][3][m] = C.c[0][m] + C.c[1][m];
-      }
-      fl[h] = sfl + (e * 9 + k) * NF;
-#pragma unroll
-      for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[h][x][mt] = v4{0, 0, 0, 0};
-    }
-    const real *Ab = A.Asym + lane + oz;
-    int fr = 0;   // a constant at every use once unrolled
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      real qt[HT][3][4];
-#pragma unroll
-      for (int h = 0; h < HT; ++h)
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-          real v[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) v[j] = qf[h][m][(nodes[ks] >> (8 * j)) & 255];
-          sym4(v, qt[h][m]);
-        }
-#pragma unroll
-      for (int p = 1; p < 4; ++p)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (!S::kstep(ks, i)) continue;
-          real y[HT];
-#pragma unroll
-          for (int h = 0; h < HT; ++h)
-            y[h] = cs[h][p][0] * qt[h][0][i] + cs[h][p][1] * qt[h][1][i] +
-                   cs[h][p][2] * qt[h][2][i];
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt, ++fr) {
-            const real af = Ab[fr * 64];
-#pragma unroll
-            for (int h = 0; h < HT; ++h)
-              acc[h][i ^ p][mt] = M::mma(af, y[h], acc[h][i ^ p][mt]);
-          }
-        }
-    }
-#pragma unroll
-    for (int ks = 0; ks < S::KF; ++ks) {
-      // the rows past Nfp of the last k-step read a valid node; their
-      // operator entries are zero
-      const int j = 4 * ks + g, jj = j < Nfp ? j : Nfp - 1;
-      real ft[HT][4];
-#pragma unroll
-      for (int h = 0; h < HT; ++h) {
-        real v[4];
-#pragma unroll
-        for (int f = 0; f < 4; ++f) v[f] = fl[h][4 * jj + f];
-        sym4(v, ft[h]);
-      }
-#pragma unroll
-      for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt, ++fr) {
-          const real af = Ab[fr * 64];
-#pragma unroll
-          for (int h = 0; h < HT; ++h) acc[h][x][mt] = M::mma(af, ft[h][x], acc[h][x][mt]);
-        }
-    }
-  }
-  Update<N, real, BE> U(A, k0, shot, nE, qout, res, tid);
-  __syncthreads();   // every wave is done with the flux buffer
-  // right-hand side to LDS in the block's (element, field, node) order;
-  // register r of this lane holds orbit 16 mt + 4 r + g
-  if (w < NT) {
-#pragma unroll
-    for (int h = 0; h < HT; ++h) {
-      const int col = (w + h * NW) * 16 + (lane & 15);
-      if (col < 9 * nE) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const real a[4] = {acc[h][0][ks / 4][ks % 4], acc[h][1][ks / 4][ks % 4],
-                             acc[h][2][ks / 4][ks % 4], acc[h][3][ks / 4][ks % 4]};
-          real t[4];
-          sym4(a, t);
-          if (4 * ks + g < S::nO)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-              sfl[col * Np + ((nodes[ks] >> (8 * j)) & 255)] = t[j];
-        }
-      }
-    }
-  }
-  __syncthreads();
-  U.apply(A, sq, sfl, ssig, nE, k0, shot, step, tid);
+  U.apply(A, sq, sfl, ssig, nE, src - k0, shot, step, tid);
 }
 
 // Phase 3 on the vector ALUs: one thread per (element, node).  AN:
@@ -660,6 +525,258 @@ __device__ __forceinline__ void phase3_nodes(const StageArgs<real> &A, const rea
   }
 }
 
+// fn(integral_constant) for every index of [I, E), as straight code
+template <int I, int E, class F>
+__device__ __forceinline__ void unroll(F &&fn) {
+  if constexpr (I < E) {
+    fn(std::integral_constant<int, I>{});
+    unroll<I + 1, E>(fn);
+  }
+}
+
+// The transform over the Klein four-group (sym.h), its own inverse up to 4.
+template <typename real>
+__device__ __forceinline__ void sym4(const real (&a)[4], real (&t)[4]) {
+  const real s = a[0] + a[1], d = a[0] - a[1], u = a[2] + a[3], v = a[2] - a[3];
+  t[0] = s + u;
+  t[1] = s - u;
+  t[2] = d + v;
+  t[3] = d - v;
+}
+
+// Phase 3 on the matrix cores in FP64 from order 3: the block's right-hand side
+// as one GEMM in the symmetry components of the lattice (sym.h).  With cs_p
+// the sum of the two coefficients c_a, a != p, of a column, component x of its
+// right-hand side is
+//   r_x = sum_p A_{x,p} (sum_m cs_p[m] q^_{m, x xor p}) + B_x F^_x,
+// the factor -1/8 in A and 1/4 in B.  Rows and products run over the
+// components' indices (sym.h) in steps of four: lane group g supplies index
+// 4 ks + g of an operand and holds row 4 r + g of accumulator r, so a lane
+// reads the four nodes of its own orbits from the LDS tile and transforms
+// them in registers (which serves all twelve blocks), and transforms its
+// results back.  The flux of a face node and its three images is one
+// transform too.  The values of the size-2 orbits sit in other lanes in
+// component 0 than in their own, and move between them.
+//
+// The instruction is the four-block 4x4x4: its four blocks take the sixteen
+// columns of a 16x16x4 with the four rows of A repeated, so rows come in fours
+// (the components have 11, 8, 8 and 8 at order 4), and it is the faster one:
+// 19.6 cycles for 256 products against 122.7 for 1024 (a loop on every SIMD, in
+// cycles of 2.4 GHz).  Matrix and vector instructions of one wave do not
+// overlap, those of two waves do.
+//
+// Its operand traffic is what the layout is made for.  Read from global memory
+// per wave, the fragments took 45 of 267 us (512 bytes to the registers for
+// 128 in memory, and every wave reads all), and no other load could be in
+// flight behind them.  So a work-group stages them in LDS (12.3 KB at order 4;
+// in chunks, one while the other is used, at orders 5 and 6: 37 and 61 KB),
+// the lifted flux keeps six quantities per face node instead of nine, which
+// leaves three work-groups a CU at order 4 (226 -> 212 us), and the residual
+// is loaded with the neighbour traces, its trip over before the update waits
+// for it (259 -> 225 us with two work-groups a CU).
+//
+// Measured, FP64 stage launch, nodal form on 16x16x4 (at order 6 the faster
+// node-per-thread form) -> these components on 16x16x4 with operators from
+// global memory -> this: order 4, 82944 elements, 348 -> 268 -> 212 us (983 MB
+// of traffic, 4.6 of the 5.3 TB/s a copy reaches), anisotropic 462 -> 362 ->
+// 256 us; order 3, 24576 elements, 54 -> 58 -> 49 us; order 5, 24576
+// elements, 211 -> 137 -> 128 us; order 6, 24576 elements, 476 -> 282 -> 217
+// us.  Orders 1 and 2 keep the nodal form, whose operators are a few
+// fragments: 34 against 44 us at order 1 and 53 against 56 us at order 2
+// (55566 elements).
+template <int N, typename real, int BE, bool AN>
+struct SymGemm {
+  using S = Sym<N>;
+  static constexpr int Np = S::Np, Nfp = S::Nfp, KS = S::KS;
+  static constexpr int ROW = 4 * Nfp | 1;         // flux row, odd against bank conflicts
+  // operator buffer: one chunk, or two where there are more
+  static constexpr int OPS1 = 16 * S::max_chunk(), OPS = OPS1 * (S::chunks > 1 ? 2 : 1);
+  static constexpr int OV = (8 * S::max_chunk() + kThreads - 1) / kThreads;
+  typedef real vec2 __attribute__((ext_vector_type(2)));
+  static constexpr int NT = (9 * BE + 15) / 16;   // column tiles
+  static_assert(NT <= kThreads / 64, "one column tile per wave");
+  int g, w, col, cols, lane;
+  const uint32_t (&nodes)[KS];
+  const real *qf[3], *fl[3], *Ab;
+  bool vel;
+  vec2 op, opv[OV];
+  real cs[4][3];
+  real acc[4][KS];   // acc[x][r] exists for r < S::steps(x)
+
+  __device__ __forceinline__ SymGemm(const StageArgs<real> &A, const real *sq,
+                                     const real *sfl, const real *sop, const double *smeta,
+                                     int nE, int64_t k0, const uint32_t (&nd)[KS], int tid)
+      : nodes(nd) {
+    lane = tid & 63;
+    g = lane >> 4;
+    w = tid >> 6;
+    col = w * 16 + (lane & 15);
+    cols = 9 * nE;
+    const bool cok = col < cols;
+    const int e = cok ? col / 9 : 0, k = cok ? col - 9 * (col / 9) : 0;
+    Column<real> C;
+    column_setup<real, AN>(A, smeta + e * DGW_META, k0 + e, k, C);
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      qf[m] = sq + (e * 9 + C.f[m]) * Np;
+      cs[1][m] = C.c[1][m] + C.c[2][m];
+      cs[2][m] = C.c[0][m] + C.c[2][m];
+      cs[3][m] = C.c[0][m] + C.c[1][m];
+    }
+    vel = k < 3;
+    fl[0] = sfl + (e * 6 + (vel ? k : 3 + C.f[0])) * ROW;
+    fl[1] = sfl + (e * 6 + (vel ? k : 3 + C.f[1])) * ROW;
+    fl[2] = sfl + (e * 6 + (vel ? k : 3 + C.f[2])) * ROW;
+    Ab = sop + 2 * (4 * g + (lane & 3));
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int r = 0; r < KS; ++r) acc[x][r] = (real)0;
+  }
+
+  // Staging of the operator chunks (sym.h): thread tid's vectors of chunk c
+  // into registers, and from there to its LDS buffer; chunk 0 comes with the
+  // block's first loads, chunk c + 1 while chunk c is used.
+  static __device__ __forceinline__ void load_ops(const StageArgs<real> &A, int c, int tid,
+                                                  vec2 (&v)[OV]) {
+    const vec2 *src = (const vec2 *)A.Asym + 8 * S::layout.begin[c];
+#pragma unroll
+    for (int u = 0; u < OV; ++u) {
+      const int t = tid + u * kThreads;
+      v[u] = src[t < 8 * S::chunk_frags(c) ? t : 0];
+    }
+  }
+  static __device__ __forceinline__ void store_ops(real *sop, int c, int tid,
+                                                   const vec2 (&v)[OV]) {
+#pragma unroll
+    for (int u = 0; u < OV; ++u) {
+      const int t = tid + u * kThreads;
+      if (t < 8 * S::chunk_frags(c)) ((vec2 *)(sop + (c & 1) * OPS1))[t] = v[u];
+    }
+  }
+
+  // acc += fragment f x y
+  template <int s>
+  __device__ __forceinline__ void mma(int n, real y, real &c) {
+    // fragment n of step s, in pairs of one 16-byte read
+    constexpr int ch = S::layout.chunk[s];
+    const int f = S::layout.at[s] - S::layout.begin[ch] + n;
+    if (f % 2 == 0 || n == 0) op = *(const vec2 *)(Ab + (ch & 1) * OPS1 + 32 * (f / 2));
+    c = __builtin_amdgcn_mfma_f64_4x4x4f64(op[f % 2], y, c, 0, 0, 0);
+  }
+  // the value of the lane `shift` groups on, for the same column
+  __device__ __forceinline__ real from(real v, int shift) const {
+    return __shfl(v, (lane + 16 * shift) & 63);
+  }
+
+  // runs step s around fn, with the staging of the next chunk
+  template <int s, class F>
+  __device__ __forceinline__ void step(const StageArgs<real> &A, real *sop, int tid, F &&fn) {
+    constexpr int c = S::layout.chunk[s];
+    constexpr bool next = c + 1 < S::chunks;
+    if constexpr (next && (s == 0 || S::layout.chunk[s > 0 ? s - 1 : 0] != c))
+      load_ops(A, c + 1, tid, opv);
+    if (w < NT) fn();
+    if constexpr (next && S::layout.chunk[s + 1 < S::nsteps ? s + 1 : s] != c) {
+      store_ops(sop, c + 1, tid, opv);
+      __syncthreads();
+    }
+  }
+
+  __device__ __forceinline__ void volume(const StageArgs<real> &A, real *sop, int tid) {
+    real mv[4][3];   // components 2 and 3 of their short orbits, at their indices' lanes
+    unroll<0, KS>([&](auto I) {
+      constexpr int s = decltype(I)::value, ks = KS - 1 - s;
+      step<s>(A, sop, tid, [&] {
+        real qt[3][4];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+          real v[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) v[j] = qf[m][(nodes[ks] >> (8 * j)) & 255];
+          sym4(v, qt[m]);
+#pragma unroll
+          for (int t = 2; t < 4; ++t) {
+            if (S::nt > 0 && ks == S::home(t) / 4) mv[t][m] = from(qt[m][t], S::shift(t));
+            if (S::nt > 0 && ks == S::nf / 4)
+              qt[m][t] = g >= S::nf % 4 && g < S::nf % 4 + S::nt ? mv[t][m] : qt[m][t];
+          }
+        }
+        int n = 0;   // a constant at every use once unrolled
+#pragma unroll
+        for (int p = 1; p < 4; ++p)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if (ks >= S::steps(i)) continue;
+            const real y = cs[p][0] * qt[0][i] + cs[p][1] * qt[1][i] + cs[p][2] * qt[2][i];
+#pragma unroll
+            for (int r = 0; r < S::steps(i ^ p); ++r) mma<s>(n++, y, acc[i ^ p][r]);
+          }
+      });
+    });
+  }
+
+  __device__ __forceinline__ void lift(const StageArgs<real> &A, real *sop, int tid) {
+    // a stress column's flux on face n is sum_m cf[n][m] dv_m with the same
+    // coefficients as its volume term on Fscale_n n_n = -4 grad lambda_n, the
+    // transform of cs; a velocity column's flux is stored as it is
+    real cf[4][3];
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      const real c[4] = {(real)0, cs[1][m], cs[2][m], cs[3][m]};
+      real t[4];
+      sym4(c, t);
+#pragma unroll
+      for (int n = 0; n < 4; ++n) cf[n][m] = vel ? (real)(m == 0) : t[n];
+    }
+    unroll<0, S::KF>([&](auto I) {
+      constexpr int ks = decltype(I)::value, s = KS + ks;
+      step<s>(A, sop, tid, [&] {
+        // the rows past Nfp of the last step read a valid node; their
+        // operator entries are zero
+        const int j = 4 * ks + g, jj = j < Nfp ? j : Nfp - 1;
+        real v[4], ft[4];
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+          v[n] = cf[n][0] * fl[0][n * Nfp + jj] + cf[n][1] * fl[1][n * Nfp + jj] +
+                 cf[n][2] * fl[2][n * Nfp + jj];
+        sym4(v, ft);
+        int n = 0;
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+          for (int r = 0; r < S::steps(x); ++r) mma<s>(n++, ft[x], acc[x][r]);
+      });
+    });
+  }
+
+  // right-hand side to LDS in the block's (element, field, node) order
+  __device__ __forceinline__ void store(real *out) const {
+    if (w >= NT) return;
+    real mv[4] = {};
+    if (S::nt > 0)
+#pragma unroll
+      for (int t = 2; t < 4; ++t) mv[t] = from(acc[t][S::nf / 4], -S::shift(t));
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      real a[4], t[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        a[x] = ks < S::steps(x) ? acc[x][ks] : (real)0;
+        if (S::nt > 0 && x >= 2) {
+          if (ks == S::nf / 4 && g >= S::nf % 4 && g < S::nf % 4 + S::nt) a[x] = (real)0;
+          if (ks == S::home(x) / 4 && g >= S::home(x) % 4 && g < S::home(x) % 4 + S::nt)
+            a[x] = mv[x];
+        }
+      }
+      sym4(a, t);
+      if (4 * ks + g < S::nO && col < cols)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[col * Np + ((nodes[ks] >> (8 * j)) & 255)] = t[j];
+    }
+  }
+};
+
 // Face tables of a block for this thread's face items: the packed
 // connectivity code and, for interior faces, the neighbour trace's offset
 // in the shot's field array.  Loaded ahead of the gathers (by the persistent
@@ -670,18 +787,20 @@ struct FaceTab {
   static constexpr int FI = (BE * 4 * Sz<N>::Nfp + kThreads - 1) / kThreads;
   int cn[FI];
   int64_t gb[FI];
-  int n1[FI];   // the face node's volume node in its own element, and its
-                // slot in the matrix-core form's flux row << 16
+  int n1[FI];   // the face node's volume node in its own element
 };
 
-template <int N, typename real, int BE>
+// SY: with each face's nodes in the order of their face-0 preimages (sym.h)
+template <int N, typename real, int BE, bool SY>
 __device__ __forceinline__ void face_tables(const StageArgs<real> &A, int64_t item,
-                                            int64_t nblk, FaceTab<N, BE> &T) {
+                                            int64_t nblk, int64_t total,
+                                            FaceTab<N, BE> &T) {
   constexpr int Np = Sz<N>::Np, Nfp = Sz<N>::Nfp, NF = 4 * Nfp;
-  const int slot = (int)(item / nblk);
-  const int shot = A.shot_map ? A.shot_map[slot] : slot;
+  const int slot = slot_of(item, nblk, total);
   const int64_t k0 = (item - (int64_t)slot * nblk) * BE;
   const int nE = (int)((A.K - k0) < BE ? (A.K - k0) : BE);
+  const uint8_t *nbn = SY ? A.nbsym : A.nbnode;
+  const int32_t *own = SY ? A.fsym : A.fmask;
 #pragma unroll
   for (int u = 0; u < FaceTab<N, BE>::FI; ++u) {
     const int t = threadIdx.x + u * kThreads;
@@ -690,9 +809,9 @@ __device__ __forceinline__ void face_tables(const StageArgs<real> &A, int64_t it
     const int e = tt / NF, fm = tt - e * NF, f = fm / Nfp;
     const int64_t k = ok ? k0 + e : 0;
     const int cn = A.conn[k * 4 + f];
-    const int nb = A.nbnode[k * NF + fm];
+    const int nb = nbn[k * NF + fm];
     T.cn[u] = ok ? cn : CONN_ABSORB;
-    T.n1[u] = A.fslot[fm];
+    T.n1[u] = own[fm];
     // masked arithmetic rather than a select, so the compiler keeps the
     // node-table load unconditional (not behind a wait for cn)
     const int64_t live = -(int64_t)(ok && cn >= 0);
@@ -716,11 +835,12 @@ struct BlockLoad {
 
 template <int N, typename real, int BE>
 __device__ __forceinline__ void block_loads(const StageArgs<real> &A, int64_t item,
-                                            int64_t nblk, BlockLoad<N, real, BE> &B) {
+                                            int64_t nblk, int64_t total,
+                                            BlockLoad<N, real, BE> &B) {
   constexpr int Np = Sz<N>::Np;
   using BL = BlockLoad<N, real, BE>;
   using SP = typename BL::SP;
-  const int slot = (int)(item / nblk);
+  const int slot = slot_of(item, nblk, total);
   const int shot = A.shot_map ? A.shot_map[slot] : slot;
   const int64_t k0 = (item - (int64_t)slot * nblk) * BE;
   const int nE = (int)((A.K - k0) < BE ? (A.K - k0) : BE);
@@ -756,19 +876,166 @@ __device__ __forceinline__ void block_loads(const StageArgs<real> &A, int64_t it
 }
 
 template <int N, typename real, int BE, int V>
+constexpr bool kSymV = (V == 1 || V == 3) && kSymForm<N, real>;
+
+// Exact Riemann flux of one face node: own trace from LDS, neighbour trace qp
+// (registers), lifted quantities to LDS at d: six adjacent values (the
+// node-per-thread forms), or at stride st six (symmetry components, dv without
+// Fscale) or all nine components (nodal GEMM).
+template <int N, typename real, int V>
+__device__ __forceinline__ void face_flux(const StageArgs<real> &A, const real *qe,
+                                          const double *g, int64_t k, int cn, int n1, int f,
+                                          const real (&qp)[9], real *d, int st) {
+  constexpr int Np = Sz<N>::Np;
+  real qm[9], p[9];
+#pragma unroll
+  for (int c = 0; c < 9; ++c) qm[c] = qe[c * Np + n1];
+  if (cn >= 0) {
+#pragma unroll
+    for (int c = 0; c < 9; ++c) p[c] = qp[c];
+  } else if (cn == CONN_FREE) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) p[c] = qm[c];
+#pragma unroll
+    for (int c = 3; c < 9; ++c) p[c] = -qm[c];
+  } else {
+#pragma unroll
+    for (int c = 0; c < 9; ++c) p[c] = (real)0;
+  }
+  const real nx = (real)g[M_NORMAL + 3 * f], ny = (real)g[M_NORMAL + 3 * f + 1],
+             nz = (real)g[M_NORMAL + 3 * f + 2];
+  // jumps [v] = v+ - v-, [t] = (sigma+ - sigma-) n
+  const real dvx = p[0] - qm[0], dvy = p[1] - qm[1], dvz = p[2] - qm[2];
+  const real dsxx = p[3] - qm[3], dsyy = p[4] - qm[4], dszz = p[5] - qm[5];
+  const real dsyz = p[6] - qm[6], dsxz = p[7] - qm[7], dsxy = p[8] - qm[8];
+  const real dtx = dsxx * nx + dsxy * ny + dsxz * nz;
+  const real dty = dsxy * nx + dsyy * ny + dsyz * nz;
+  const real dtz = dsxz * nx + dsyz * ny + dszz * nz;
+  const real ri = (real)g[M_RHOINV], fs = (real)g[M_FSCALE + f];
+  // traction change t* - t- (w) and velocity change dv = v* - v- (u) of
+  // the flux states: tu times the exact Riemann states' plus (1 - tu)
+  // times the central states' (half the jumps); tu = 1 (upwind) leaves
+  // exactly the Riemann terms (1 x + 0 = x)
+  const real tu = A.ftau, hc = ((real)1 - tu) * (real)0.5;
+  real wx, wy, wz, ux, uy, uz;
+  if constexpr (V == 2 || V == 3) {
+    // anisotropic: dv = W ([t] + Z+ [v]) and t* - t- = Z- dv with the
+    // face's impedance matrices (symmetric 3x3: xx yy zz yz xz xy)
+    const double *za = A.aniso + k * DGW_ANI + A_FACE + A_FSTRIDE * f;
+    auto smv = [](const double *Z, real x, real y, real z, real (&o)[3]) {
+      const real xx = (real)Z[0], yy = (real)Z[1], zz = (real)Z[2], yz = (real)Z[3],
+                 xz = (real)Z[4], xy = (real)Z[5];
+      o[0] = xx * x + xy * y + xz * z;
+      o[1] = xy * x + yy * y + yz * z;
+      o[2] = xz * x + yz * y + zz * z;
+    };
+    real zj[3], dv[3], dtr[3];
+    smv(za + A_ZP, dvx, dvy, dvz, zj);
+    smv(za + A_W, dtx + zj[0], dty + zj[1], dtz + zj[2], dv);
+    smv(za + A_ZM, dv[0], dv[1], dv[2], dtr);
+    wx = tu * dtr[0] + hc * dtx;
+    wy = tu * dtr[1] + hc * dty;
+    wz = tu * dtr[2] + hc * dtz;
+    ux = tu * dv[0] + hc * dvx;
+    uy = tu * dv[1] + hc * dvy;
+    uz = tu * dv[2] + hc * dvz;
+  } else {
+    const real dvn = dvx * nx + dvy * ny + dvz * nz;
+    const real dtn = dtx * nx + dty * ny + dtz * nz;
+    const real zp = (real)g[M_ZP], zs = (real)g[M_ZS];
+    const real zpn = (real)g[M_ZPNB + f], zsn = (real)g[M_ZSNB + f];
+    const real izp = (real)g[M_IZPS + f], izs = (real)g[M_IZSS + f];
+    // normal and tangential Riemann amplitudes
+    const real kn = (dtn + zpn * dvn) * izp;
+    const real kTx = (dtx - dtn * nx + zsn * (dvx - dvn * nx)) * izs;
+    const real kTy = (dty - dtn * ny + zsn * (dvy - dvn * ny)) * izs;
+    const real kTz = (dtz - dtn * nz + zsn * (dvz - dvn * nz)) * izs;
+    wx = tu * (zp * kn * nx + zs * kTx) + hc * dtx;
+    wy = tu * (zp * kn * ny + zs * kTy) + hc * dty;
+    wz = tu * (zp * kn * nz + zs * kTz) + hc * dtz;
+    ux = tu * (kn * nx + kTx) + hc * dvx;
+    uy = tu * (kn * ny + kTy) + hc * dvy;
+    uz = tu * (kn * nz + kTz) + hc * dvz;
+  }
+  // velocity flux (t* - t-)/rho and the velocity change dv; the stress
+  // flux is lambda (n.dv) I + mu (dv n^T + n dv^T) (anisotropic: C N(n) dv)
+  // with n constant on the face, so lifting dv is enough for all six
+  // stress components
+  if constexpr (kSymV<N, real, 1, V>) {
+    d[0 * st] = fs * wx * ri;
+    d[1 * st] = fs * wy * ri;
+    d[2 * st] = fs * wz * ri;
+    d[3 * st] = ux;
+    d[4 * st] = uy;
+    d[5 * st] = uz;
+  } else if constexpr (V == 0 || V == 2) {
+    d[0] = fs * wx * ri;
+    d[1] = fs * wy * ri;
+    d[2] = fs * wz * ri;
+    d[3] = fs * ux;
+    d[4] = fs * uy;
+    d[5] = fs * uz;
+  } else {
+    // all nine lifted components, field-major (the GEMM's data side)
+    const real Dvx = fs * ux, Dvy = fs * uy, Dvz = fs * uz;
+    d[0 * st] = fs * wx * ri;
+    d[1 * st] = fs * wy * ri;
+    d[2 * st] = fs * wz * ri;
+    if constexpr (V == 3) {
+      // C N(n) dv
+      const real ev[6] = {nx * Dvx, ny * Dvy, nz * Dvz, nz * Dvy + ny * Dvz,
+                          nz * Dvx + nx * Dvz, ny * Dvx + nx * Dvy};
+      const double *Cu = A.aniso + k * DGW_ANI + A_C;
+      real cm[6][6];
+      int uu = 0;
+#pragma unroll
+      for (int a = 0; a < 6; ++a)
+#pragma unroll
+        for (int b = a; b < 6; ++b) cm[a][b] = cm[b][a] = (real)Cu[uu++];
+#pragma unroll
+      for (int a = 0; a < 6; ++a) {
+        real acc = 0;
+#pragma unroll
+        for (int b = 0; b < 6; ++b) acc += cm[a][b] * ev[b];
+        d[(3 + a) * st] = acc;
+      }
+    } else {
+      const real la = (real)g[M_LAM], mu = (real)g[M_MU];
+      const real ndv = nx * Dvx + ny * Dvy + nz * Dvz;
+      d[3 * st] = la * ndv + 2 * mu * Dvx * nx;
+      d[4 * st] = la * ndv + 2 * mu * Dvy * ny;
+      d[5 * st] = la * ndv + 2 * mu * Dvz * nz;
+      d[6 * st] = mu * (Dvy * nz + Dvz * ny);
+      d[7 * st] = mu * (Dvx * nz + Dvz * nx);
+      d[8 * st] = mu * (Dvx * ny + Dvy * nx);
+    }
+  }
+}
+
+template <int N, typename real, int BE, int V>
 __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t item,
-                                           int64_t nblk, const FaceTab<N, BE> &T,
+                                           int64_t nblk, int64_t total,
+                                           const FaceTab<N, BE> &T,
                                            const BlockLoad<N, real, BE> &B) {
-  constexpr int Np = Sz<N>::Np, Nfp = Sz<N>::Nfp, NF = 4 * Sz<N>::Nfp;
-  constexpr int FI = (BE * NF + kThreads - 1) / kThreads;   // face items per thread
+  constexpr int Np = Sz<N>::Np, Nfp = Sz<N>::Nfp, NF = 4 * Nfp;
+  constexpr bool SY = kSymV<N, real, BE, V>;
+  constexpr int FI = FaceTab<N, BE>::FI;      // face items per thread
+  // flux row of an (element, field) in the matrix-core forms
+  constexpr int ROW = SY ? NF | 1 : NF;
+  // lifted flux, and in the matrix-core forms then the right-hand side
+  constexpr int FL = SY ? 6 * ROW : V == 1 || V == 3 ? 9 * NF : 6 * NF;
+  constexpr int SF = BE * (SY && FL < 9 * Np ? 9 * Np : FL);
   // declared here (not passed in) so every access stays an LDS access
   __shared__ real sq[BE * 9 * Np];
-  __shared__ __attribute__((aligned(16))) real sfl[BE * NF * (V == 1 || V == 3 ? 9 : 6)];
+  __shared__ __attribute__((aligned(16))) real sfl[SF];
   __shared__ double smeta[BE * DGW_META];
   __shared__ double ssig[BE];
-  const int slot = (int)(item / nblk);
+  using SG = SymGemm<N, double, SY ? BE : 1, V == 3>;
+  __shared__ __attribute__((aligned(16))) double sop[SY ? SG::OPS : 2];
+  const int slot = slot_of(item, nblk, total);
   const int shot = A.shot_map ? A.shot_map[slot] : slot;
   const int64_t step = A.shot_step[shot];
+  const int64_t src = A.src_elem[shot];
   if (step >= A.shot_len[shot]) return;            // uniform per work-group
   const int64_t k0 = (item - (int64_t)slot * nblk) * BE;
   // never taken (items cover the mesh exactly), but it bounds nE to
@@ -785,27 +1052,25 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
   int oz;
   asm volatile("v_mov_b32 %0, 0" : "=v"(oz));
 
-  // the nodes of this lane's orbits (sym.h), four to a word
-  constexpr bool kSym = (V == 1 || V == 3) && kSymForm<N, real>;
-  uint32_t nodes[Sym<N>::KS];
-  if constexpr (kSym)
-#pragma unroll
-    for (int ks = 0; ks < Sym<N>::KS; ++ks)
-      nodes[ks] = A.symnode[4 * ks + ((tid & 63) >> 4)];
-
   // ---- 1. all global reads of the item's fields are in flight together ----
   // neighbour traces of this thread's face nodes go to registers; read
   // unconditionally (boundary and idle face items have offset 0, an
   // in-bounds read of the first element that is never used), so no branch
   // makes the compiler wait on earlier loads
+  // the first operator chunk
+  typename SG::vec2 opv[SG::OV];
+  if constexpr (SY) SG::load_ops(A, 0, tid, opv);
   real qp[FI][9];
-  int cnv[FI];
 #pragma unroll
   for (int u = 0; u < FI; ++u) {
-    cnv[u] = T.cn[u];
 #pragma unroll
     for (int c = 0; c < 9; ++c) qp[u][c] = qin[T.gb[u] + c * Np];
   }
+  // The symmetry form reads its operators from LDS, so nothing waits behind the
+  // residual and it is loaded here.  In the nodal form every operator load
+  // would wait for it.
+  Update<N, real, BE> U;
+  if constexpr (SY) U.load(A, k0, shot, nE, qout, res, tid);
   // the block's own fields and per-element data (loads issued by
   // block_loads) to LDS
   {
@@ -830,150 +1095,46 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
       }
     }
     if (tid < nE) ssig[tid] = B.sg;
+    if constexpr (SY) SG::store_ops(sop, 0, tid, opv);
   }
   __syncthreads();
 
-  // ---- 2. faces: exact Riemann flux, six lifted quantities per node ----
+  // ---- 2. faces: exact Riemann flux ----
+  // the nodes of this lane's orbits (sym.h), four to a word, and the first
+  // operator fragments, in flight during the flux
+  uint32_t nodes[Sym<N>::KS];
+  if constexpr (SY)
+#pragma unroll
+    for (int ks = 0; ks < Sym<N>::KS; ++ks)
+      nodes[ks] = A.symnode[4 * ks + ((tid & 63) >> 4)];
 #pragma unroll
   for (int u = 0; u < FI; ++u) {
     const int t = tid + u * kThreads;
     if (t >= nE * NF) continue;
-    const int e = t / NF, fm = t - e * NF, f = fm / Nfp;
-    const double *g = smeta + e * DGW_META;
-    const real *qe = sq + e * 9 * Np;
-    const int n1 = T.n1[u] & 0xffff;
-    real qm[9], p[9];
-#pragma unroll
-    for (int c = 0; c < 9; ++c) qm[c] = qe[c * Np + n1];
-    const int cn = cnv[u];
-    if (cn >= 0) {
-#pragma unroll
-      for (int c = 0; c < 9; ++c) p[c] = qp[u][c];
-    } else if (cn == CONN_FREE) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) p[c] = qm[c];
-#pragma unroll
-      for (int c = 3; c < 9; ++c) p[c] = -qm[c];
-    } else {
-#pragma unroll
-      for (int c = 0; c < 9; ++c) p[c] = (real)0;
-    }
-    const real nx = (real)g[M_NORMAL + 3 * f], ny = (real)g[M_NORMAL + 3 * f + 1],
-               nz = (real)g[M_NORMAL + 3 * f + 2];
-    // jumps [v] = v+ - v-, [t] = (sigma+ - sigma-) n
-    const real dvx = p[0] - qm[0], dvy = p[1] - qm[1], dvz = p[2] - qm[2];
-    const real dsxx = p[3] - qm[3], dsyy = p[4] - qm[4], dszz = p[5] - qm[5];
-    const real dsyz = p[6] - qm[6], dsxz = p[7] - qm[7], dsxy = p[8] - qm[8];
-    const real dtx = dsxx * nx + dsxy * ny + dsxz * nz;
-    const real dty = dsxy * nx + dsyy * ny + dsyz * nz;
-    const real dtz = dsxz * nx + dsyz * ny + dszz * nz;
-    const real ri = (real)g[M_RHOINV], fs = (real)g[M_FSCALE + f];
-    // traction change t* - t- (w) and velocity change dv = v* - v- (u) of
-    // the flux states: tu times the exact Riemann states' plus (1 - tu)
-    // times the central states' (half the jumps); tu = 1 (upwind) leaves
-    // exactly the Riemann terms (1 x + 0 = x)
-    const real tu = A.ftau, hc = ((real)1 - tu) * (real)0.5;
-    real wx, wy, wz, ux, uy, uz;
-    if constexpr (V == 2 || V == 3) {
-      // anisotropic: dv = W ([t] + Z+ [v]) and t* - t- = Z- dv with the
-      // face's impedance matrices (symmetric 3x3: xx yy zz yz xz xy)
-      const double *za = A.aniso + (k0 + e) * DGW_ANI + A_FACE + A_FSTRIDE * f;
-      auto smv = [](const double *Z, real x, real y, real z, real (&o)[3]) {
-        const real xx = (real)Z[0], yy = (real)Z[1], zz = (real)Z[2], yz = (real)Z[3],
-                   xz = (real)Z[4], xy = (real)Z[5];
-        o[0] = xx * x + xy * y + xz * z;
-        o[1] = xy * x + yy * y + yz * z;
-        o[2] = xz * x + yz * y + zz * z;
-      };
-      real zj[3], dv[3], dtr[3];
-      smv(za + A_ZP, dvx, dvy, dvz, zj);
-      smv(za + A_W, dtx + zj[0], dty + zj[1], dtz + zj[2], dv);
-      smv(za + A_ZM, dv[0], dv[1], dv[2], dtr);
-      wx = tu * dtr[0] + hc * dtx;
-      wy = tu * dtr[1] + hc * dty;
-      wz = tu * dtr[2] + hc * dtz;
-      ux = tu * dv[0] + hc * dvx;
-      uy = tu * dv[1] + hc * dvy;
-      uz = tu * dv[2] + hc * dvz;
-    } else {
-      const real dvn = dvx * nx + dvy * ny + dvz * nz;
-      const real dtn = dtx * nx + dty * ny + dtz * nz;
-      const real zp = (real)g[M_ZP], zs = (real)g[M_ZS];
-      const real zpn = (real)g[M_ZPNB + f], zsn = (real)g[M_ZSNB + f];
-      const real izp = (real)g[M_IZPS + f], izs = (real)g[M_IZSS + f];
-      // normal and tangential Riemann amplitudes
-      const real kn = (dtn + zpn * dvn) * izp;
-      const real kTx = (dtx - dtn * nx + zsn * (dvx - dvn * nx)) * izs;
-      const real kTy = (dty - dtn * ny + zsn * (dvy - dvn * ny)) * izs;
-      const real kTz = (dtz - dtn * nz + zsn * (dvz - dvn * nz)) * izs;
-      wx = tu * (zp * kn * nx + zs * kTx) + hc * dtx;
-      wy = tu * (zp * kn * ny + zs * kTy) + hc * dty;
-      wz = tu * (zp * kn * nz + zs * kTz) + hc * dtz;
-      ux = tu * (kn * nx + kTx) + hc * dvx;
-      uy = tu * (kn * ny + kTy) + hc * dvy;
-      uz = tu * (kn * nz + kTz) + hc * dvz;
-    }
-    // velocity flux (t* - t-)/rho and the velocity change dv; the stress
-    // flux is lambda (n.dv) I + mu (dv n^T + n dv^T) (anisotropic: C N(n) dv)
-    // with n constant on the face, so lifting dv is enough for all six
-    // stress components
-    if constexpr (V == 0 || V == 2) {
-      real *d = sfl + (e * NF + fm) * 6;
-      d[0] = fs * wx * ri;
-      d[1] = fs * wy * ri;
-      d[2] = fs * wz * ri;
-      d[3] = fs * ux;
-      d[4] = fs * uy;
-      d[5] = fs * uz;
-    } else {
-      // all nine lifted components, field-major (the GEMM's data side)
-      const real Dvx = fs * ux, Dvy = fs * uy, Dvz = fs * uz;
-      real *d = sfl + e * 9 * NF + (kSymForm<N, real> ? T.n1[u] >> 16 : fm);
-      d[0 * NF] = fs * wx * ri;
-      d[1 * NF] = fs * wy * ri;
-      d[2 * NF] = fs * wz * ri;
-      if constexpr (V == 3) {
-        // C N(n) dv
-        const real ev[6] = {nx * Dvx, ny * Dvy, nz * Dvz, nz * Dvy + ny * Dvz,
-                            nz * Dvx + nx * Dvz, ny * Dvx + nx * Dvy};
-        const double *Cu = A.aniso + (k0 + e) * DGW_ANI + A_C;
-        real cm[6][6];
-        int uu = 0;
-#pragma unroll
-        for (int a = 0; a < 6; ++a)
-#pragma unroll
-          for (int b = a; b < 6; ++b) cm[a][b] = cm[b][a] = (real)Cu[uu++];
-#pragma unroll
-        for (int a = 0; a < 6; ++a) {
-          real acc = 0;
-#pragma unroll
-          for (int b = 0; b < 6; ++b) acc += cm[a][b] * ev[b];
-          d[(3 + a) * NF] = acc;
-        }
-      } else {
-        const real la = (real)g[M_LAM], mu = (real)g[M_MU];
-        const real ndv = nx * Dvx + ny * Dvy + nz * Dvz;
-        d[3 * NF] = la * ndv + 2 * mu * Dvx * nx;
-        d[4 * NF] = la * ndv + 2 * mu * Dvy * ny;
-        d[5 * NF] = la * ndv + 2 * mu * Dvz * nz;
-        d[6 * NF] = mu * (Dvy * nz + Dvz * ny);
-        d[7 * NF] = mu * (Dvx * nz + Dvz * nx);
-        d[8 * NF] = mu * (Dvx * ny + Dvy * nx);
-      }
-    }
+    const int e = t / NF, fm = t - e * NF;
+    real *d = V == 0 || V == 2 ? sfl + t * 6 : sfl + e * (SY ? 6 : 9) * ROW + fm;
+    face_flux<N, real, V>(A, sq + e * 9 * Np, smeta + e * DGW_META, k0 + e, T.cn[u], T.n1[u],
+                          fm / Nfp, qp[u], d, ROW);
   }
-  __syncthreads();
-
-
-  if constexpr (kSym)
-    phase3_sym<N, real, BE, V == 3>(A, sq, sfl, smeta, ssig, nE, k0, shot, step, qout, res,
-                                    nodes, oz, tid);
-  else if constexpr (V == 1 || V == 3)
-    phase3_mfma<N, real, BE, V == 3>(A, sq, sfl, smeta, ssig, nE, k0, shot, step, qout, res,
-                                     oz, tid);
-  else
-    phase3_nodes<N, real, BE, V == 2>(A, sq, sfl, smeta, ssig, nE, k0, shot, step, qout,
-                                      res, oz, tid);
+  // ---- 3. volume, lift, update ----
+  if constexpr (SY) {
+    SymGemm<N, real, BE, V == 3> G(A, sq, sfl, sop, smeta, nE, k0, nodes, tid);
+    G.volume(A, sop, tid);
+    __syncthreads();
+    G.lift(A, sop, tid);
+    __syncthreads();   // every wave is done with the flux buffer
+    G.store(sfl);
+    __syncthreads();
+    U.apply(A, sq, sfl, ssig, nE, src - k0, shot, step, tid);
+  } else {
+    __syncthreads();
+    if constexpr (V == 1 || V == 3)
+      phase3_mfma<N, real, BE, V == 3>(A, sq, sfl, smeta, ssig, nE, k0, shot, step, src, qout,
+                                       res, oz, tid);
+    else
+      phase3_nodes<N, real, BE, V == 2>(A, sq, sfl, smeta, ssig, nE, k0, shot, step, qout,
+                                        res, oz, tid);
+  }
 }
 
 // One work-group per item.
@@ -982,10 +1143,10 @@ __global__ void __launch_bounds__(kThreads)
 stage_kernel(StageArgs<real> A, int64_t nblk, int64_t total) {
   const int64_t item = xcd_item(blockIdx.x, total);
   FaceTab<N, BE> T;
-  face_tables<N, real, BE>(A, item, nblk, T);
+  face_tables<N, real, BE, kSymV<N, real, BE, V>>(A, item, nblk, total, T);
   BlockLoad<N, real, BE> B;
-  block_loads<N, real, BE>(A, item, nblk, B);
-  stage_item<N, real, BE, V>(A, item, nblk, T, B);
+  block_loads<N, real, BE>(A, item, nblk, total, B);
+  stage_item<N, real, BE, V>(A, item, nblk, total, T, B);
 }
 
 // Persistent grid (a multiple of 8 work-groups) looping over the items;
@@ -995,15 +1156,15 @@ __global__ void __launch_bounds__(kThreads)
 stage_kernel_persistent(StageArgs<real> A, int64_t nblk, int64_t total) {
   int64_t L = blockIdx.x;
   FaceTab<N, BE> T;
-  if (L < total) face_tables<N, real, BE>(A, xcd_item(L, total), nblk, T);
+  if (L < total) face_tables<N, real, BE, kSymV<N, real, BE, V>>(A, xcd_item(L, total), nblk, total, T);
   for (; L < total; L += gridDim.x) {
     const int64_t item = xcd_item(L, total);
     FaceTab<N, BE> Tn;
     if (L + gridDim.x < total)
-      face_tables<N, real, BE>(A, xcd_item(L + gridDim.x, total), nblk, Tn);
+      face_tables<N, real, BE, kSymV<N, real, BE, V>>(A, xcd_item(L + gridDim.x, total), nblk, total, Tn);
     BlockLoad<N, real, BE> B;
-    block_loads<N, real, BE>(A, item, nblk, B);
-    stage_item<N, real, BE, V>(A, item, nblk, T, B);
+    block_loads<N, real, BE>(A, item, nblk, total, B);
+    stage_item<N, real, BE, V>(A, item, nblk, total, T, B);
     __syncthreads();   // LDS is reused by the next item
     T = Tn;
   }
@@ -1047,7 +1208,7 @@ hipError_t launch_t(int be, int wpc, int ncu, int nshots, const StageArgs<real> 
                     hipStream_t st) {
   constexpr int A_ = Shapes<N, real, V>::a, B_ = Shapes<N, real, V>::b;
   if (be != A_ && be != B_) return hipErrorInvalidValue;
-  if ((V == 1 || V == 3) && (kSymForm<N, real> ? a.Asym == nullptr || a.symnode == nullptr
+  if ((V == 1 || V == 3) && (kSymForm<N, real> ? a.Asym == nullptr || a.nbsym == nullptr
                                     : a.Avol == nullptr || a.Alift == nullptr))
     return hipErrorInvalidValue;
   const int64_t nblk = (a.K + be - 1) / be;

@@ -25,10 +25,18 @@ __device__ inline double ricker_d(double tau, double f0, double t0, double amp) 
 // Linear work-group id -> item index such that each XCD (id % 8) owns one
 // contiguous range of items.
 __device__ inline int64_t xcd_item(int64_t L, int64_t total) {
-  const int x = (int)(L & 7);
-  int64_t start = 0;
-  for (int y = 0; y < x; ++y) start += (total - y + 7) >> 3;
-  return start + (L >> 3);
+  const int64_t x = L & 7, r = total & 7;
+  return x * (total >> 3) + (x < r ? x : r) + (L >> 3);
+}
+
+// Launch slot of an item (items of a slot are consecutive, nblk to a slot).
+// The general 64-bit division costs about 200 dependent scalar instructions
+// ahead of a work-group's first load; one slot needs none, and counts below
+// 2^32 a short one.
+__device__ inline int slot_of(int64_t item, int64_t nblk, int64_t total) {
+  if (total == nblk) return 0;
+  if ((total >> 32) == 0) return (int)((uint32_t)item / (uint32_t)nblk);
+  return (int)(item / nblk);
 }
 
 template <typename real>

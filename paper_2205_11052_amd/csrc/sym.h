@@ -45,7 +45,7 @@ struct Sym {
     int n = 0;                 // orbits: full ones, then size 2 by stabiliser, then size 1
     uint8_t at[Np][4] = {};    // at[o][j] = node g_j b_o
     uint8_t stab[Np] = {};     // 0 full; 1..3 fixed by that g; 4 fixed by all
-    uint8_t slot[4 * Nfp] = {};  // face node (f, m) -> 4 j + f, j its face-0 preimage
+    uint8_t face[4 * Nfp] = {};  // (f, j) -> face node (f, m) with face-0 preimage j
   };
   static constexpr Tab make() {
     Tab T;
@@ -85,7 +85,7 @@ struct Sym {
                   if (node(i2, j2, k2) == want) at = c;
                   ++c;
                 }
-            T.slot[f * Nfp + m] = (uint8_t)(4 * at + f);
+            T.face[f * Nfp + at] = (uint8_t)(f * Nfp + m);
             ++m;
           }
     }
@@ -93,28 +93,79 @@ struct Sym {
   }
   static constexpr Tab tab = make();
   static constexpr int nO = tab.n;
-  static constexpr int MT = (nO + 15) / 16;   // row tiles of 16 orbits
-  static constexpr int KS = (nO + 3) / 4;     // k-steps of 4 orbits
-  static constexpr int KF = (Nfp + 3) / 4;    // k-steps of the lift
-  // whether orbit o has a component i
-  static constexpr bool has(int o, int i) {
-    return o < nO && (tab.stab[o] == 0 || i == 0 || tab.stab[o] == i);
-  }
-  static constexpr bool kstep(int ks, int i) {
-    for (int o = 4 * ks; o < 4 * ks + 4; ++o)
-      if (has(o, i)) return true;
-    return false;
-  }
-  // fragments of 64 entries: volume in the order (ks, p, i, row tile) of the
-  // k-steps that exist, then lift in the order (ks, i, row tile)
-  static constexpr int volume_frags() {
+  static constexpr int KS = (nO + 3) / 4;     // steps of four orbits
+  static constexpr int KF = (Nfp + 3) / 4;    // steps of the lift
+  // full orbits, and size-2 orbits of each type (stabiliser)
+  static constexpr int count(int st) {
     int n = 0;
-    for (int ks = 0; ks < KS; ++ks)
-      for (int p = 1; p < 4; ++p)
-        for (int i = 0; i < 4; ++i) n += kstep(ks, i) ? MT : 0;
+    for (int o = 0; o < nO; ++o) n += tab.stab[o] == st ? 1 : 0;
     return n;
   }
-  static constexpr int frags() { return volume_frags() + 4 * KF * MT; }
+  static constexpr int nf = count(0), nt = count(1);
+  // Component x has dim(x) values: index n < nf is orbit n, then come the
+  // size-2 orbits that have the component (type x; component 0 has all, type
+  // by type, and the size-1 orbit last, so its index is the orbit).
+  static constexpr int dim(int x) { return x == 0 ? nO : nf + nt; }
+  static constexpr int steps(int x) { return (dim(x) + 3) / 4; }
+  static constexpr int orbit(int x, int n) {
+    return n >= dim(x) ? -1 : n < nf || x == 0 ? n : nf + (x - 1) * nt + n - nf;
+  }
+  // index in component 0 (and lane group mod 4, step) of the first type-t
+  // orbit; in component t its index is nf.  shift(t): lane groups from the
+  // latter's to the former's
+  static constexpr int home(int t) { return nf + (t - 1) * nt; }
+  static constexpr int shift(int t) { return home(t) % 4 - nf % 4; }
+  // nt consecutive indices from nf, and from home(t), lie in one step
+  static constexpr bool aligned() {
+    return nt == 0 || (nf % 4 + nt <= 4 && home(2) % 4 + nt <= 4 && home(3) % 4 + nt <= 4);
+  }
+  static_assert(aligned() && count(2) == nt && count(3) == nt, "short orbits within a step");
+  // Operator fragments of 16 entries (4 rows x 4 products), step by step: the
+  // volume's steps from the last down, each in the order (p, input component
+  // i, row step of component i xor p), then the lift's, each in the order
+  // (component, row step).  The steps are grouped in chunks that the kernel
+  // stages in LDS one after the other (orders 3 and 4: all in one), each
+  // starting at an even fragment.
+  static constexpr int nsteps = KS + KF;
+  static constexpr int step_frags(int s) {
+    if (s >= KS) return steps(0) + steps(1) + steps(2) + steps(3);
+    int n = 0;
+    for (int p = 1; p < 4; ++p)
+      for (int i = 0; i < 4; ++i) n += KS - 1 - s < steps(i) ? steps(i ^ p) : 0;
+    return n;
+  }
+  static constexpr int kLimit = N <= 4 ? 100 : N == 5 ? 48 : 78;
+  struct Layout {
+    int chunk[nsteps] = {}, at[nsteps] = {};   // chunk and first fragment of a step
+    int begin[nsteps + 1] = {};                // first fragment of a chunk
+    int chunks = 0;
+  };
+  static constexpr Layout lay() {
+    Layout L;
+    int f = 0, in = kLimit + 1;
+    for (int s = 0; s < nsteps; ++s) {
+      if (in + step_frags(s) > kLimit) {
+        f += f % 2;
+        L.begin[L.chunks++] = f;
+        in = 0;
+      }
+      L.chunk[s] = L.chunks - 1;
+      L.at[s] = f;
+      f += step_frags(s);
+      in += step_frags(s);
+    }
+    L.begin[L.chunks] = f + f % 2;
+    return L;
+  }
+  static constexpr Layout layout = lay();
+  static constexpr int chunks = layout.chunks;
+  static constexpr int frags = layout.begin[chunks];
+  static constexpr int chunk_frags(int c) { return layout.begin[c + 1] - layout.begin[c]; }
+  static constexpr int max_chunk() {
+    int m = 0;
+    for (int c = 0; c < chunks; ++c) m = chunk_frags(c) > m ? chunk_frags(c) : m;
+    return m;
+  }
 };
 
 }  // namespace dgw
