@@ -87,6 +87,8 @@ struct dgw_ctx {
   double *d_rec_w = nullptr, *d_trace = nullptr;
   std::vector<int32_t> h_nrec, h_rec_elem;
   std::vector<double> h_rec_w;
+  double *d_conv = nullptr;         // [conv_n] piece of a converted transfer (FP32)
+  size_t conv_n = 0;
   double *d_partial = nullptr;
   int *d_flag = nullptr;
 
@@ -153,6 +155,9 @@ struct dgw_ctx {
   int upload(void *dst, const void *src, size_t bytes);
   int download(void *dst, const void *src, size_t bytes);
   size_t real_size() const;
+  int put_real(void *dst, const double *src, size_t n);        // host FP64 -> reals
+  int get_real(double *dst, const void *src, size_t n);        // reals -> host FP64
+  bool conv_scratch(size_t n);
   void invalidate_graph();
   int upload_operators();
   int alloc_shots();

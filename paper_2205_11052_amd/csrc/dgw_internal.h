@@ -258,6 +258,9 @@ hipError_t launch_energy(int precision, const void *q, int64_t K, int Np,
                          double *partial, int nblocks, hipStream_t st);
 hipError_t launch_finite(int precision, const void *q, int64_t n, int *flag,
                          hipStream_t st);
+// n values converted, FP64 -> FP32 and FP32 -> FP64
+hipError_t launch_narrow(const double *in, float *out, int64_t n, hipStream_t st);
+hipError_t launch_widen(const float *in, double *out, int64_t n, hipStream_t st);
 // Supported elements-per-block values for an order / precision.
 std::vector<int> stage_block_choices(int kernel, int N, int precision);
 int default_block(int kernel, int N, int precision);

@@ -108,6 +108,31 @@ __global__ void __launch_bounds__(256) finite_kernel(const real *q, int64_t n,
   if (bad) atomicOr(flag, 1);
 }
 
+// Bound by the link the values then cross (about 25 GB/s); one value a thread
+// and iteration, coalesced.
+template <typename A, typename B>
+__global__ void __launch_bounds__(256) convert_kernel(const A *in, B *out, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    out[i] = (B)in[i];
+}
+
+template <typename A, typename B>
+hipError_t launch_convert(const A *in, B *out, int64_t n, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  const int64_t nb = (n + 255) / 256;
+  hipLaunchKernelGGL((convert_kernel<A, B>), dim3((unsigned)(nb < 4096 ? nb : 4096)), dim3(256),
+                     0, st, in, out, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_narrow(const double *in, float *out, int64_t n, hipStream_t st) {
+  return launch_convert(in, out, n, st);
+}
+hipError_t launch_widen(const float *in, double *out, int64_t n, hipStream_t st) {
+  return launch_convert(in, out, n, st);
+}
+
 template <typename real>
 hipError_t launch_receivers_t(int nshots, const RecArgs &a, hipStream_t st) {
   switch (a.Np) {
