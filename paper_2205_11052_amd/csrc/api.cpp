@@ -582,6 +582,10 @@ int dgw_ctx::enqueue_pml(const void *in, void *out, int stage, bool timed) {
     a.DsT = (const real *)d_DsT;
     a.DtT = (const real *)d_DtT;
     a.LIFTT = (const real *)d_LIFTT;
+    a.Asym = (const real *)d_Asym;
+    a.symnode = d_symnode;
+    a.nbsym = d_nbsym;
+    a.fsym = d_fsym;
     a.fmask = d_fmask;
     a.nP = pml_n;
     a.shot_stride = mesh.K * 9 * R.Np;

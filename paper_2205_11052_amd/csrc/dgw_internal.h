@@ -142,6 +142,10 @@ struct PmlArgs {
   const int32_t *conn;
   const uint8_t *nbnode;
   const real *DrT, *DsT, *DtT, *LIFTT;
+  const real *Asym;             // as in StageArgs
+  const uint32_t *symnode;
+  const uint8_t *nbsym;
+  const int32_t *fsym;
   const int32_t *fmask;
   int64_t nP;
   int64_t shot_stride;          // K * 9 * Np

@@ -27,19 +27,19 @@
 //   3. the volume terms and the lifted flux, by one of three forms: one thread
 //      per (element, node) on the vector ALUs (phase3_nodes); a GEMM on the
 //      matrix cores in nodal form (phase3_mfma: FP32, and FP64 at orders 1 and
-//      2); a GEMM in the symmetry components of the lattice (SymGemm: FP64
+//      2); a GEMM in the symmetry components of the lattice (StageGemm: FP64
 //      from order 3).  Then + point source, res = a res + dt rhs and
 //      q_out = q_in + b res.
 // q_in and q_out are distinct buffers (neighbour traces are read from q_in
 // while other blocks write q_out); res is element-local and updated in place.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
-#include <type_traits>
 
 #include "dgw_internal.h"
 #include "stage_common.h"
-#include "sym.h"
+#include "sym_gemm.h"
 
 namespace dgw {
 
@@ -47,7 +47,7 @@ namespace {
 
 constexpr int kThreads = 256;
 // Whether the matrix-core form of a precision works in symmetry components
-// (SymGemm): FP64.  FP32 keeps the nodal form's order of summation, and with
+// (StageGemm): FP64.  FP32 keeps the nodal form's order of summation, and with
 // it its results to the last bit.
 template <int N, typename real>
 constexpr bool kSymForm = N >= 3 && sizeof(real) == 8;
@@ -525,25 +525,6 @@ __device__ __forceinline__ void phase3_nodes(const StageArgs<real> &A, const rea
   }
 }
 
-// fn(integral_constant) for every index of [I, E), as straight code
-template <int I, int E, class F>
-__device__ __forceinline__ void unroll(F &&fn) {
-  if constexpr (I < E) {
-    fn(std::integral_constant<int, I>{});
-    unroll<I + 1, E>(fn);
-  }
-}
-
-// The transform over the Klein four-group (sym.h), its own inverse up to 4.
-template <typename real>
-__device__ __forceinline__ void sym4(const real (&a)[4], real (&t)[4]) {
-  const real s = a[0] + a[1], d = a[0] - a[1], u = a[2] + a[3], v = a[2] - a[3];
-  t[0] = s + u;
-  t[1] = s - u;
-  t[2] = d + v;
-  t[3] = d - v;
-}
-
 // Phase 3 on the matrix cores in FP64 from order 3: the block's right-hand side
 // as one GEMM in the symmetry components of the lattice (sym.h).  With cs_p
 // the sum of the two coefficients c_a, a != p, of a column, component x of its
@@ -584,195 +565,43 @@ __device__ __forceinline__ void sym4(const real (&a)[4], real (&t)[4]) {
 // us.  Orders 1 and 2 keep the nodal form, whose operators are a few
 // fragments: 34 against 44 us at order 1 and 53 against 56 us at order 2
 // (55566 elements).
-template <int N, typename real, int BE, bool AN>
-struct SymGemm {
-  using S = Sym<N>;
-  static constexpr int Np = S::Np, Nfp = S::Nfp, KS = S::KS;
-  static constexpr int ROW = 4 * Nfp | 1;         // flux row, odd against bank conflicts
-  // operator buffer: one chunk, or two where there are more
-  static constexpr int OPS1 = 16 * S::max_chunk(), OPS = OPS1 * (S::chunks > 1 ? 2 : 1);
-  static constexpr int OV = (8 * S::max_chunk() + kThreads - 1) / kThreads;
-  typedef real vec2 __attribute__((ext_vector_type(2)));
-  static constexpr int NT = (9 * BE + 15) / 16;   // column tiles
-  static_assert(NT <= kThreads / 64, "one column tile per wave");
-  int g, w, col, cols, lane;
-  const uint32_t (&nodes)[KS];
-  const real *qf[3], *fl[3], *Ab;
-  bool vel;
-  vec2 op, opv[OV];
-  real cs[4][3];
-  real acc[4][KS];   // acc[x][r] exists for r < S::steps(x)
+template <int N, int BE, bool AN>
+struct StageGemm : SymGemm<N, 3, (9 * BE + 15) / 16, kThreads> {
+  using G = SymGemm<N, 3, (9 * BE + 15) / 16, kThreads>;
+  bool vel, ok;
 
-  __device__ __forceinline__ SymGemm(const StageArgs<real> &A, const real *sq,
-                                     const real *sfl, const real *sop, const double *smeta,
-                                     int nE, int64_t k0, const uint32_t (&nd)[KS], int tid)
-      : nodes(nd) {
-    lane = tid & 63;
-    g = lane >> 4;
-    w = tid >> 6;
-    col = w * 16 + (lane & 15);
-    cols = 9 * nE;
-    const bool cok = col < cols;
-    const int e = cok ? col / 9 : 0, k = cok ? col - 9 * (col / 9) : 0;
-    Column<real> C;
-    column_setup<real, AN>(A, smeta + e * DGW_META, k0 + e, k, C);
-#pragma unroll
-    for (int m = 0; m < 3; ++m) {
-      qf[m] = sq + (e * 9 + C.f[m]) * Np;
-      cs[1][m] = C.c[1][m] + C.c[2][m];
-      cs[2][m] = C.c[0][m] + C.c[2][m];
-      cs[3][m] = C.c[0][m] + C.c[1][m];
-    }
+  __device__ __forceinline__ StageGemm(const StageArgs<double> &A, const double *sq,
+                                       const double *sfl, const double *sop,
+                                       const double *smeta, int nE, int64_t k0,
+                                       const uint32_t (&nd)[G::KS], int tid)
+      : G(sop, nd, tid) {
+    const int col = G::column();
+    ok = col < 9 * nE;
+    const int e = ok ? col / 9 : 0, k = ok ? col - 9 * (col / 9) : 0;
+    Column<double> C;
+    column_setup<double, AN>(A, smeta + e * DGW_META, k0 + e, k, C);
     vel = k < 3;
-    fl[0] = sfl + (e * 6 + (vel ? k : 3 + C.f[0])) * ROW;
-    fl[1] = sfl + (e * 6 + (vel ? k : 3 + C.f[1])) * ROW;
-    fl[2] = sfl + (e * 6 + (vel ? k : 3 + C.f[2])) * ROW;
-    Ab = sop + 2 * (4 * g + (lane & 3));
-#pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-      for (int r = 0; r < KS; ++r) acc[x][r] = (real)0;
-  }
-
-  // Staging of the operator chunks (sym.h): thread tid's vectors of chunk c
-  // into registers, and from there to its LDS buffer; chunk 0 comes with the
-  // block's first loads, chunk c + 1 while chunk c is used.
-  static __device__ __forceinline__ void load_ops(const StageArgs<real> &A, int c, int tid,
-                                                  vec2 (&v)[OV]) {
-    const vec2 *src = (const vec2 *)A.Asym + 8 * S::layout.begin[c];
-#pragma unroll
-    for (int u = 0; u < OV; ++u) {
-      const int t = tid + u * kThreads;
-      v[u] = src[t < 8 * S::chunk_frags(c) ? t : 0];
-    }
-  }
-  static __device__ __forceinline__ void store_ops(real *sop, int c, int tid,
-                                                   const vec2 (&v)[OV]) {
-#pragma unroll
-    for (int u = 0; u < OV; ++u) {
-      const int t = tid + u * kThreads;
-      if (t < 8 * S::chunk_frags(c)) ((vec2 *)(sop + (c & 1) * OPS1))[t] = v[u];
-    }
-  }
-
-  // acc += fragment f x y
-  template <int s>
-  __device__ __forceinline__ void mma(int n, real y, real &c) {
-    // fragment n of step s, in pairs of one 16-byte read
-    constexpr int ch = S::layout.chunk[s];
-    const int f = S::layout.at[s] - S::layout.begin[ch] + n;
-    if (f % 2 == 0 || n == 0) op = *(const vec2 *)(Ab + (ch & 1) * OPS1 + 32 * (f / 2));
-    c = __builtin_amdgcn_mfma_f64_4x4x4f64(op[f % 2], y, c, 0, 0, 0);
-  }
-  // the value of the lane `shift` groups on, for the same column
-  __device__ __forceinline__ real from(real v, int shift) const {
-    return __shfl(v, (lane + 16 * shift) & 63);
-  }
-
-  // runs step s around fn, with the staging of the next chunk
-  template <int s, class F>
-  __device__ __forceinline__ void step(const StageArgs<real> &A, real *sop, int tid, F &&fn) {
-    constexpr int c = S::layout.chunk[s];
-    constexpr bool next = c + 1 < S::chunks;
-    if constexpr (next && (s == 0 || S::layout.chunk[s > 0 ? s - 1 : 0] != c))
-      load_ops(A, c + 1, tid, opv);
-    if (w < NT) fn();
-    if constexpr (next && S::layout.chunk[s + 1 < S::nsteps ? s + 1 : s] != c) {
-      store_ops(sop, c + 1, tid, opv);
-      __syncthreads();
-    }
-  }
-
-  __device__ __forceinline__ void volume(const StageArgs<real> &A, real *sop, int tid) {
-    real mv[4][3];   // components 2 and 3 of their short orbits, at their indices' lanes
-    unroll<0, KS>([&](auto I) {
-      constexpr int s = decltype(I)::value, ks = KS - 1 - s;
-      step<s>(A, sop, tid, [&] {
-        real qt[3][4];
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-          real v[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) v[j] = qf[m][(nodes[ks] >> (8 * j)) & 255];
-          sym4(v, qt[m]);
-#pragma unroll
-          for (int t = 2; t < 4; ++t) {
-            if (S::nt > 0 && ks == S::home(t) / 4) mv[t][m] = from(qt[m][t], S::shift(t));
-            if (S::nt > 0 && ks == S::nf / 4)
-              qt[m][t] = g >= S::nf % 4 && g < S::nf % 4 + S::nt ? mv[t][m] : qt[m][t];
-          }
-        }
-        int n = 0;   // a constant at every use once unrolled
-#pragma unroll
-        for (int p = 1; p < 4; ++p)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            if (ks >= S::steps(i)) continue;
-            const real y = cs[p][0] * qt[0][i] + cs[p][1] * qt[1][i] + cs[p][2] * qt[2][i];
-#pragma unroll
-            for (int r = 0; r < S::steps(i ^ p); ++r) mma<s>(n++, y, acc[i ^ p][r]);
-          }
-      });
-    });
-  }
-
-  __device__ __forceinline__ void lift(const StageArgs<real> &A, real *sop, int tid) {
-    // a stress column's flux on face n is sum_m cf[n][m] dv_m with the same
-    // coefficients as its volume term on Fscale_n n_n = -4 grad lambda_n, the
-    // transform of cs; a velocity column's flux is stored as it is
-    real cf[4][3];
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
-      const real c[4] = {(real)0, cs[1][m], cs[2][m], cs[3][m]};
-      real t[4];
+      G::qf[m] = sq + (e * 9 + C.f[m]) * G::Np;
+      G::cs[1][m] = C.c[1][m] + C.c[2][m];
+      G::cs[2][m] = C.c[0][m] + C.c[2][m];
+      G::cs[3][m] = C.c[0][m] + C.c[1][m];
+      G::fl[m] = sfl + (e * 6 + (vel ? k : 3 + C.f[m])) * G::ROW;
+    }
+  }
+
+  // a stress column's flux on face n is sum_m cf[n][m] dv_m with the same
+  // coefficients as its volume term on Fscale_n n_n = -4 grad lambda_n, the
+  // transform of cs; a velocity column's flux is stored as it is
+  __device__ __forceinline__ void face(double (&cf)[4][3]) const {
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      const double c[4] = {0.0, G::cs[1][m], G::cs[2][m], G::cs[3][m]};
+      double t[4];
       sym4(c, t);
 #pragma unroll
-      for (int n = 0; n < 4; ++n) cf[n][m] = vel ? (real)(m == 0) : t[n];
-    }
-    unroll<0, S::KF>([&](auto I) {
-      constexpr int ks = decltype(I)::value, s = KS + ks;
-      step<s>(A, sop, tid, [&] {
-        // the rows past Nfp of the last step read a valid node; their
-        // operator entries are zero
-        const int j = 4 * ks + g, jj = j < Nfp ? j : Nfp - 1;
-        real v[4], ft[4];
-#pragma unroll
-        for (int n = 0; n < 4; ++n)
-          v[n] = cf[n][0] * fl[0][n * Nfp + jj] + cf[n][1] * fl[1][n * Nfp + jj] +
-                 cf[n][2] * fl[2][n * Nfp + jj];
-        sym4(v, ft);
-        int n = 0;
-#pragma unroll
-        for (int x = 0; x < 4; ++x)
-#pragma unroll
-          for (int r = 0; r < S::steps(x); ++r) mma<s>(n++, ft[x], acc[x][r]);
-      });
-    });
-  }
-
-  // right-hand side to LDS in the block's (element, field, node) order
-  __device__ __forceinline__ void store(real *out) const {
-    if (w >= NT) return;
-    real mv[4] = {};
-    if (S::nt > 0)
-#pragma unroll
-      for (int t = 2; t < 4; ++t) mv[t] = from(acc[t][S::nf / 4], -S::shift(t));
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      real a[4], t[4];
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        a[x] = ks < S::steps(x) ? acc[x][ks] : (real)0;
-        if (S::nt > 0 && x >= 2) {
-          if (ks == S::nf / 4 && g >= S::nf % 4 && g < S::nf % 4 + S::nt) a[x] = (real)0;
-          if (ks == S::home(x) / 4 && g >= S::home(x) % 4 && g < S::home(x) % 4 + S::nt)
-            a[x] = mv[x];
-        }
-      }
-      sym4(a, t);
-      if (4 * ks + g < S::nO && col < cols)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) out[col * Np + ((nodes[ks] >> (8 * j)) & 255)] = t[j];
+      for (int n = 0; n < 4; ++n) cf[n][m] = vel ? (double)(m == 0) : t[n];
     }
   }
 };
@@ -1030,7 +859,7 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
   __shared__ __attribute__((aligned(16))) real sfl[SF];
   __shared__ double smeta[BE * DGW_META];
   __shared__ double ssig[BE];
-  using SG = SymGemm<N, double, SY ? BE : 1, V == 3>;
+  using SG = StageGemm<N, SY ? BE : 1, V == 3>;
   __shared__ __attribute__((aligned(16))) double sop[SY ? SG::OPS : 2];
   const int slot = slot_of(item, nblk, total);
   const int shot = A.shot_map ? A.shot_map[slot] : slot;
@@ -1059,7 +888,7 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
   // makes the compiler wait on earlier loads
   // the first operator chunk
   typename SG::vec2 opv[SG::OV];
-  if constexpr (SY) SG::load_ops(A, 0, tid, opv);
+  if constexpr (SY) SG::load_ops(A.Asym, 0, tid, opv);
   real qp[FI][9];
 #pragma unroll
   for (int u = 0; u < FI; ++u) {
@@ -1118,12 +947,12 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
   }
   // ---- 3. volume, lift, update ----
   if constexpr (SY) {
-    SymGemm<N, real, BE, V == 3> G(A, sq, sfl, sop, smeta, nE, k0, nodes, tid);
-    G.volume(A, sop, tid);
+    SG G(A, sq, sfl, sop, smeta, nE, k0, nodes, tid);
+    G.volume(A.Asym, sop, tid);
     __syncthreads();
-    G.lift(A, sop, tid);
+    G.lift(A.Asym, sop, tid, [&](double (&cf)[4][3]) { G.face(cf); });
     __syncthreads();   // every wave is done with the flux buffer
-    G.store(sfl);
+    G.store(sfl + G.column() * Np, G.ok);
     __syncthreads();
     U.apply(A, sq, sfl, ssig, nE, src - k0, shot, step, tid);
   } else {

@@ -8,6 +8,7 @@ import pytest
 import torch
 
 import workloads as W
+from oracle import pml as OP
 from gpu_helpers import oracle_problem, oracle_run, random_fields, rel_l2, say
 from paper_2205_11052_amd import Solver
 
@@ -32,8 +33,8 @@ def test_blocks(N, prec, n, aniso):
     else:
         rng = np.random.default_rng(60 + N)
         cp = rng.uniform(1.5, 3.0, K)
-        rho, lam, mu = W.medium.lame_from_velocities(cp, cp / rng.uniform(1.5, 2.2, K),
-                                                     rng.uniform(1.0, 3.0, K))
+        rho, lam, mu = W.lame_from_velocities(cp, cp / rng.uniform(1.5, 2.2, K),
+                                              rng.uniform(1.0, 3.0, K))
     dt = P.suggest_dt(rho, lam, mu, 0.5)
     if aniso:
         lam, mu = np.ones(K), np.ones(K)
@@ -56,3 +57,37 @@ def test_blocks(N, prec, n, aniso):
             err = rel_l2(s.get_fields(0), q_ora)
             say("N=%d fp%d K=%d be=%d wpc=%d aniso=%s %.3e" % (N, prec, K, be, wpc, aniso, err))
             assert err <= (1e-12 if prec == 64 else 1e-5)
+
+
+@pytest.mark.parametrize("m", [1, 3, 7, 8, 23])
+@pytest.mark.parametrize("N", [3, 4, 5, 6])
+def test_layer_blocks(N, m):
+    """The layer kernel in FP64 on one element, less than a block, a block, a
+    block and a remainder, and several: fields and memory variables against
+    the oracle (<= 1e-12)."""
+    mesh = W.general_mesh(2, L=1.0, seed=80 + N)
+    K = mesh["etov"].shape[0]
+    P = oracle_problem(mesh, N)
+    rng = np.random.default_rng(90 + m)
+    cp = rng.uniform(1.5, 3.0, K)
+    rho, lam, mu = W.lame_from_velocities(cp, cp / rng.uniform(1.5, 2.2, K),
+                                          rng.uniform(1.0, 3.0, K))
+    dt = P.suggest_dt(rho, lam, mu, 0.5)
+    el = np.sort(rng.choice(K, m, replace=False)).astype(np.int32)
+    prof = rng.uniform(0.0, 5.0, (m, 6, P.Np))
+    d, a = np.zeros((K, 3, P.Np)), np.zeros((K, 3, P.Np))
+    d[el], a[el] = prof[:, :3], prof[:, 3:]
+    q0 = random_fields(K, P.Np, 95 + N)
+    t = torch.as_tensor
+    q_ora, m_ora, _ = OP.run(P, t(q0).clone(), t(rho), t(lam), t(mu), t(d), t(a), dt, 3)
+    s = Solver(N, 64, 1)
+    s.set_mesh_dict(mesh)
+    s.set_material(rho, lam, mu)
+    s.set_dt(dt)
+    s.set_pml(el, prof)
+    s.set_fields(0, q0)
+    s.step(3)
+    err = rel_l2(s.get_fields(0), q_ora.numpy())
+    merr = rel_l2(s.pml_memory(0), m_ora.numpy()[el])
+    say("N=%d layer elements %d fields %.3e memory %.3e" % (N, m, err, merr))
+    assert err <= 1e-12 and merr <= 1e-12
