@@ -358,7 +358,8 @@ int dgw_set_stiffness(dgw_ctx *ctx, const double *C);
 /* Launch shape of the stage kernel.  kernel 0: one thread per (element,
  * node) with the block's fields and lifted fluxes staged in LDS; then
  * elems_per_block is the elements per work-group (0 = default; DGW_EINVAL for
- * values the kernel does not implement) and wgs_per_cu the work-groups per
+ * values the kernel does not implement; FP64 from order 2 on runs kernel 1's
+ * code in a block of its own choice here) and wgs_per_cu the work-groups per
  * compute unit of a persistent grid (0 = one work-group per block of
  * elements, the default; 1..64 = a persistent grid of that many work-groups
  * per CU, rounded up to a multiple of 8, looping over the blocks of all

@@ -237,8 +237,8 @@ hipError_t launch_set_steps(int64_t *steps, int nshots, int64_t value,
                             hipStream_t st);
 
 // Launchers (kernels.hip); return the launch error.
-// kernel 0 (one thread per element node on the vector ALUs), 1 (the
-// volume and lift contractions as one GEMM on the matrix cores), both with
+// kernel 0 (one thread per element node on the vector ALUs; FP64 from order 2
+// on as kernel 1), 1 (the volume and lift contractions as one GEMM on the matrix cores), both with
 // 256 threads per work-group, with args.aniso set each running its
 // anisotropic form, or 2 (the minimal-form matrix-core kernel of
 // stage_split.hip; isotropic only): be = elements per work-group,
@@ -247,6 +247,8 @@ hipError_t launch_set_steps(int64_t *steps, int nshots, int64_t value,
 hipError_t launch_stage(int kernel, int N, int precision, int be, int wpc,
                         int ncu, int nshots, const void *args, hipStream_t st);
 bool stage_kernel_supported(int kernel, int N, int precision);
+// Whether kernel 0 of an order and precision runs kernel 1's code.
+bool stage_zero_is_one(int N, int precision);
 // Kernel 2 (stage_split.hip): the minimal-form matrix-core kernel, 16
 // elements per work-group, isotropic elements only, orders 1-4 in FP64 and
 // 1-6 in FP32.

@@ -1089,23 +1089,44 @@ hipError_t launch_stage(int kernel, int N, int precision, int be, int wpc, int n
     if (be != stage_split_block() || wpc != 0) return hipErrorInvalidValue;
     return launch_stage_split(N, precision, nshots, args, st);
   }
+  if (kernel == 0 && stage_zero_is_one(N, precision)) {
+    const std::vector<int> own = stage_block_choices(0, N, precision),
+                           one = stage_block_choices(1, N, precision);
+    if (std::find(own.begin(), own.end(), be) == own.end()) return hipErrorInvalidValue;
+    kernel = 1;
+    const int64_t elems = ((const StageArgs<double> *)args)->K * nshots;
+    be = 3 * ((elems + one[0] - 1) / one[0]) < ncu ? one[1] : one[0];
+  }
   // anisotropic elements: instantiations 2 (node per thread) and 3 (matrix
   // cores)
   const bool an = precision == 64 ? ((const StageArgs<double> *)args)->aniso != nullptr
                                   : ((const StageArgs<float> *)args)->aniso != nullptr;
   if (an) {
     if (precision == 64)
-      return kernel == 0 ? launch_r<double, 2>(N, be, wpc, ncu, nshots, args, st)
+      return kernel == 0 ? launch_t<1, double, 2>(be, wpc, ncu, nshots,
+                                                  *(const StageArgs<double> *)args, st)
                          : launch_r<double, 3>(N, be, wpc, ncu, nshots, args, st);
     return kernel == 0 ? launch_r<float, 2>(N, be, wpc, ncu, nshots, args, st)
                        : launch_r<float, 3>(N, be, wpc, ncu, nshots, args, st);
   }
   if (precision == 64)
-    return kernel == 0 ? launch_r<double, 0>(N, be, wpc, ncu, nshots, args, st)
+    return kernel == 0 ? launch_t<1, double, 0>(be, wpc, ncu, nshots,
+                                                *(const StageArgs<double> *)args, st)
                        : launch_r<double, 1>(N, be, wpc, ncu, nshots, args, st);
   return kernel == 0 ? launch_r<float, 0>(N, be, wpc, ncu, nshots, args, st)
                      : launch_r<float, 1>(N, be, wpc, ncu, nshots, args, st);
 }
+
+// Kernel 0 in FP64 from order 2 runs kernel 1's code (each element's results do
+// not depend on the block): the node-per-thread form is slower there at every
+// size.  Stage launch, node per thread -> kernel 1: order 2, 55566 elements, 58
+// -> 54 us, 384 elements 10.8 -> 7.7; order 3, 384 elements, 14.9 -> 9.4, 7986
+// elements 26 -> 23; order 4, 82944 elements, 433 -> 212; order 6, 7986
+// elements, 151 -> 78.  The larger block, but the smaller one where that
+// leaves two thirds of the CUs without a work-group (order 4, 384 elements,
+// 12.0 -> 10.7 us; 1296 elements 12.9 against 13.7).  Order 1 keeps it: 30
+// against 35 us at 55566 elements.
+bool stage_zero_is_one(int N, int precision) { return precision == 64 && N >= 2; }
 
 bool stage_kernel_supported(int kernel, int N, int precision) {
   if (kernel == 2) return stage_split_supported(N, precision);
