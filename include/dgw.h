@@ -272,7 +272,9 @@ int dgw_set_adjoint_memory(dgw_ctx *ctx, int64_t bytes);
  * changed) and keep the fastest; if cache_path is not NULL the choice is read
  * from / written to that JSON file (keyed by order, precision, element count
  * and shot count).  The chosen shape is returned through the two pointers
- * (either may be NULL); see dgw_set_launch. */
+ * (either may be NULL); see dgw_set_launch.  In FP32, where the kernels round
+ * differently, the kernel follows from the order and the element and shot
+ * counts and only its shape is timed. */
 int dgw_autotune(dgw_ctx *ctx, const char *cache_path, int *kernel,
                  int *elems_per_block, int *wgs_per_cu);
 

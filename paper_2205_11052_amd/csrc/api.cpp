@@ -14,6 +14,7 @@
 #include "../../include/dgw.h"
 #include "dgw_internal.h"
 #include "dgw_ctx.h"
+#include "nodal.h"
 #include "sym.h"
 
 using namespace dgw;
@@ -260,6 +261,44 @@ static void sym_tables(const RefElem &R, std::vector<double> &frag,
   order.assign(S::tab.face, S::tab.face + NF);
 }
 
+// Fragments of the nodal matrix-core form (nodal.h), VW of them side by side per
+// lane (16 bytes), lane l holding row l % 16 and product l / 16 of a 16x4 tile,
+// and the nodes of the accumulator rows.
+template <int N>
+static void nodal_tables(const RefElem &R, int precision, std::vector<double> &frag,
+                         std::vector<uint32_t> &rows) {
+  using S = Nodal<N>;
+  const int VW = precision == 64 ? 2 : 4;
+  frag.assign((size_t)S::frags * 64, 0.0);
+  const std::vector<double> *D[3] = {&R.Dr, &R.Ds, &R.Dt};
+  for (int s = 0; s < S::nsteps; ++s) {
+    int f = S::layout.at[s];
+    for (int mt = 0; mt < S::MT; ++mt) {
+      if (!S::need(s, mt)) continue;
+      for (int l = 0; l < 64; ++l) {
+        const int i = S::tab.row[16 * mt + l % 16];
+        if (i >= S::Np) continue;
+        double v = 0;
+        if (s < 3 * S::KS) {
+          const int j = 4 * (s % S::KS) + l / 16;
+          if (j < S::Np) v = (*D[s / S::KS])[(size_t)i * S::Np + j];
+        } else {
+          v = R.LIFT[(size_t)i * S::NF + 4 * (s - 3 * S::KS) + l / 16];
+        }
+        frag[((size_t)(f / VW) * 64 + l) * VW + f % VW] = v;
+      }
+      ++f;
+    }
+  }
+  rows.assign(4 * S::MT, 0);
+  for (int mt = 0; mt < S::MT; ++mt)
+    for (int g = 0; g < 4; ++g)
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * mt + (precision == 64 ? g + 4 * r : 4 * g + r);
+        rows[4 * mt + g] |= (uint32_t)S::tab.row[i] << (8 * r);
+      }
+}
+
 int dgw_ctx::upload_operators() {
   const int Np = R.Np, NF = 4 * R.Nfp;
   const size_t rs = real_size();
@@ -340,6 +379,26 @@ int dgw_ctx::upload_operators() {
       if ((rc = upload(d_Alift, alf.data(), rs * alf.size()))) return rc;
       if ((rc = upload(d_Alf, aff.data(), rs * aff.size()))) return rc;
     }
+  }
+  {
+    std::vector<double> fr;
+    std::vector<uint32_t> rows;
+    switch (R.N) {
+      case 1: nodal_tables<1>(R, precision, fr, rows); break;
+      case 2: nodal_tables<2>(R, precision, fr, rows); break;
+      case 3: nodal_tables<3>(R, precision, fr, rows); break;
+      case 4: nodal_tables<4>(R, precision, fr, rows); break;
+      case 5: nodal_tables<5>(R, precision, fr, rows); break;
+      default: nodal_tables<6>(R, precision, fr, rows); break;
+    }
+    d_Anod = dalloc(rs * fr.size());
+    d_rowtab = (uint32_t *)dalloc(sizeof(uint32_t) * rows.size());
+    if (!d_Anod || !d_rowtab) return fail(DGW_ENOMEM, "device allocation failed (operators)");
+    const std::vector<float> f32(fr.begin(), fr.end());
+    if ((rc = upload(d_Anod, precision == 64 ? (const void *)fr.data() : f32.data(),
+                     rs * fr.size())))
+      return rc;
+    if ((rc = upload(d_rowtab, rows.data(), sizeof(uint32_t) * rows.size()))) return rc;
   }
   if (precision == 64) {
     std::vector<double> fr;

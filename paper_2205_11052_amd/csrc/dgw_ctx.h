@@ -68,6 +68,8 @@ struct dgw_ctx {
   void *d_Alf = nullptr;                         // per-face lift fragments
   void *d_Asym = nullptr;                        // symmetry-component fragments (sym.h)
   uint32_t *d_symnode = nullptr;
+  void *d_Anod = nullptr;                        // nodal fragments (nodal.h)
+  uint32_t *d_rowtab = nullptr;
   int32_t *d_fsym = nullptr;
   uint8_t *d_nbsym = nullptr;
   double *d_M = nullptr;
@@ -197,6 +199,8 @@ inline void stage_args(const dgw_ctx *c, dgw::StageArgs<real> &a, const void *in
   a.Alf = (const real *)c->d_Alf;
   a.Asym = (const real *)c->d_Asym;
   a.symnode = c->d_symnode;
+  a.Anod = (const real *)c->d_Anod;
+  a.rowtab = c->d_rowtab;
   a.fsym = c->d_fsym;
   a.nbsym = c->d_nbsym;
   a.fmask = c->d_fmask;

@@ -95,7 +95,11 @@ struct StageArgs {
   // bytes (FP64 contexts only, as nbsym and fsym)
   const real *Asym;
   const uint32_t *symnode;
-  // nodal operator fragments in MFMA lane order (the other forms):
+  // fragments of the nodal matrix-core form and the nodes of its tile rows
+  // (nodal.h), word [4 mt + g] = the four accumulator rows of lane group g
+  const real *Anod;
+  const uint32_t *rowtab;
+  // nodal operator fragments in MFMA lane order (kernel 2):
   // Avol[a][ks][mt][64] = D_a[16 mt + l % 16][4 ks + l / 16],
   // Alift[ks][mt][64] = LIFT[16 mt + l % 16][4 ks + l / 16], zero-padded
   const real *Avol, *Alift;

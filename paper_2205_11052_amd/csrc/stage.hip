@@ -26,7 +26,7 @@
 //      lifted dv or on the way into the lift), or all nine components;
 //   3. the volume terms and the lifted flux, by one of three forms: one thread
 //      per (element, node) on the vector ALUs (phase3_nodes); a GEMM on the
-//      matrix cores in nodal form (phase3_mfma: FP32, and FP64 at orders 1 and
+//      matrix cores in nodal form (NodalGemm: FP32, and FP64 at orders 1 and
 //      2); a GEMM in the symmetry components of the lattice (StageGemm: FP64
 //      from order 3).  Then + point source, res = a res + dt rhs and
 //      q_out = q_in + b res.
@@ -39,6 +39,7 @@
 
 #include "dgw_internal.h"
 #include "stage_common.h"
+#include "nodal.h"
 #include "sym_gemm.h"
 
 namespace dgw {
@@ -259,41 +260,56 @@ __device__ __forceinline__ void column_setup(const StageArgs<real> &A, const dou
   o.f[2] = f2;
 }
 
-// Phase 3 on the matrix cores in nodal form: the block's right-hand side
-// is one GEMM, rhs[i][(e,k)] = [Dr Ds Dt LIFT][i][.] x
-// [u_r; u_s; u_t; F][.][(e,k)], whose operator side is shared by all
-// elements: the operator fragments are pre-arranged in HBM in MFMA lane
-// order (L1/L2-resident), the data side is formed in registers from the LDS
-// tile.  Each wave owns one or two tiles of 16 columns (element, field) and
-// feeds both from every fragment it loads; rows are nodes.  The accumulators
-// go through LDS (the flux buffer, dead by then) so that the residual loads,
-// the update and the stores run over the block's contiguous span, fully
-// coalesced.
+// Phase 3 on the matrix cores in nodal form: the block's right-hand side is one
+// GEMM, rhs[i][(e,k)] = [Dr Ds Dt LIFT][i][.] x [u_r; u_s; u_t; F][.][(e,k)],
+// whose operator side is shared by all elements.  Each wave owns one or two
+// tiles of 16 columns (element, field) and feeds both from every fragment it
+// reads; rows are nodes, in the order of nodal.h.  The fragments are staged in
+// LDS in chunks, one while the other is used, without the zero tiles; the data
+// side is formed in registers from the LDS tile.  The accumulators go through
+// LDS (the flux buffer, dead by then) so that the update and the stores run
+// over the block's contiguous span, fully coalesced.
+// It is bound by the matrix instructions and the passes through LDS around
+// them.  FP32 stage launch, fragments of every tile from L2 -> this: order 4,
+// 82944 elements, 190 -> 164 us (without the fragment loads 112); order 5, 118
+// -> 96; order 6, 24576 elements, 223 -> 173 us.  A field that is not finite
+// spreads over its element in a few stages, not within one, as zero tiles are
+// left out.
 template <int N, typename real, int BE, bool AN>
-__device__ __forceinline__ void phase3_mfma(const StageArgs<real> &A, const real *sq,
-                                            real *sfl, const double *smeta,
-                                            const double *ssig, int nE,
-                                            int64_t k0, int shot, int64_t step,
-                                            int64_t src, real *qout, real *res, int oz, int tid) {
+struct NodalGemm {
+  using S = Nodal<N>;
   using M = Mma<real>;
   using v4 = typename M::v4;
-  constexpr int Np = Sz<N>::Np, NF = 4 * Sz<N>::Nfp;
-  constexpr int MT = (Np + 15) / 16;          // row tiles of 16 nodes
-  constexpr int KS = (Np + 3) / 4;            // k-steps per reference direction
-  constexpr int KL = NF / 4;                  // k-steps of the lift (4 Nfp % 4 == 0)
-  constexpr int NT = (9 * BE + 15) / 16;      // column tiles
-  constexpr int NW = kThreads / 64;
-  constexpr int HT = (NT + NW - 1) / NW;      // column tiles per wave
+  static constexpr int Np = S::Np, NF = S::NF, MT = S::MT, KS = S::KS;
+  static constexpr int NT = (9 * BE + 15) / 16;      // column tiles
+  static constexpr int NW = kThreads / 64;
+  static constexpr int HT = (NT + NW - 1) / NW;      // column tiles per wave
+  static constexpr int VW = 16 / (int)sizeof(real);  // fragments per 16-byte read
+  static constexpr int OPS1 = 64 * S::max_chunk(), OPS = OPS1 * (S::chunks > 1 ? 2 : 1);
+  static constexpr int OV = (OPS1 / VW + kThreads - 1) / kThreads;
+  typedef real vec __attribute__((ext_vector_type(VW)));
   static_assert(9 * Np <= 9 * NF, "the flux buffer holds the right-hand side");
-  const int lane = tid & 63, g = lane >> 4, w = tid >> 6;
+  int lane, g, w, cols;
+  const uint32_t (&rows)[MT];   // nodes of this lane's accumulator rows, four to a word
+  const real *qf[HT][3], *fl[HT], *Ab;
+  Column<real> C[HT];
+  vec op, opv[OV];
   v4 acc[HT][MT];
-  if (w < NT) {
-    const real *qf[HT][3], *fl[HT];
-    Column<real> C[HT];
+
+  __device__ __forceinline__ NodalGemm(const StageArgs<real> &A, const real *sq,
+                                       const real *sfl, const real *sop,
+                                       const double *smeta, int nE, int64_t k0,
+                                       const uint32_t (&rw)[MT], int tid)
+      : rows(rw) {
+    lane = tid & 63;
+    g = lane >> 4;
+    w = tid >> 6;
+    cols = 9 * nE;
+    Ab = sop + VW * lane;
 #pragma unroll
     for (int h = 0; h < HT; ++h) {
-      const int col = (w + h * NW) * 16 + (lane & 15);
-      const bool cok = col < 9 * nE;
+      const int col = column(h);
+      const bool cok = col < cols;
       const int e = cok ? col / 9 : 0, k = cok ? col - 9 * (col / 9) : 0;
       column_setup<real, AN>(A, smeta + e * DGW_META, k0 + e, k, C[h]);
 #pragma unroll
@@ -302,62 +318,93 @@ __device__ __forceinline__ void phase3_mfma(const StageArgs<real> &A, const real
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) acc[h][mt] = v4{0, 0, 0, 0};
     }
-    // volume: three reference directions, K = Np (padded to a multiple of 4)
+  }
+  __device__ __forceinline__ int column(int h) const { return (w + h * NW) * 16 + (lane & 15); }
+
+  // staging of the chunks, as in SymGemm
+  static __device__ __forceinline__ void load_ops(const real *ops, int c, int tid,
+                                                  vec (&v)[OV]) {
+    const vec *src = (const vec *)ops + 64 / VW * S::layout.begin[c];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const real *Ab = A.Avol + (size_t)a * KS * MT * 64 + lane + oz;
-      for (int ks = 0; ks < KS; ++ks) {
-        // rows past Np of the last k-step read a valid node and are zeroed
-        // (a select, not a branch, so the direction stays one basic block)
-        const int j = 4 * ks + g, jj = j < Np ? j : Np - 1;
-        real b[HT];
-#pragma unroll
-        for (int h = 0; h < HT; ++h) {
-          const real v = C[h].c[a][0] * qf[h][0][jj] + C[h].c[a][1] * qf[h][1][jj] +
-                         C[h].c[a][2] * qf[h][2][jj];
-          b[h] = j < Np ? v : (real)0;
-        }
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          const real af = Ab[(ks * MT + mt) * 64];
-#pragma unroll
-          for (int h = 0; h < HT; ++h) acc[h][mt] = M::mma(af, b[h], acc[h][mt]);
-        }
-      }
+    for (int u = 0; u < OV; ++u) {
+      const int t = tid + u * kThreads;
+      v[u] = src[t < 64 / VW * S::chunk_frags(c) ? t : 0];
     }
-    // lift: the column's flux on the 4 Nfp face nodes
-    const real *Al = A.Alift + lane + oz;
-    for (int ks = 0; ks < KL; ++ks) {
+  }
+  static __device__ __forceinline__ void store_ops(real *sop, int c, int tid,
+                                                   const vec (&v)[OV]) {
+#pragma unroll
+    for (int u = 0; u < OV; ++u) {
+      const int t = tid + u * kThreads;
+      if (t < 64 / VW * S::chunk_frags(c)) ((vec *)(sop + (c & 1) * OPS1))[t] = v[u];
+    }
+  }
+
+  // step s (nodal.h): acc += its fragments x b
+  template <int s, class F>
+  __device__ __forceinline__ void step(const real *ops, real *sop, int tid, F &&fb) {
+    constexpr int c = S::layout.chunk[s];
+    constexpr bool next = c + 1 < S::chunks;
+    if constexpr (next && (s == 0 || S::layout.chunk[s > 0 ? s - 1 : 0] != c))
+      load_ops(ops, c + 1, tid, opv);
+    if (w < NT && S::step_frags(s) > 0) {
+      real b[HT];
+#pragma unroll
+      for (int h = 0; h < HT; ++h) b[h] = fb(h);
+      int f = S::layout.at[s] - S::layout.begin[c];   // constants once unrolled
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
-        const real af = Al[(ks * MT + mt) * 64];
+        if (!S::need(s, mt)) continue;
+        if (f % VW == 0) op = *(const vec *)(Ab + (c & 1) * OPS1 + 64 * f);
 #pragma unroll
-        for (int h = 0; h < HT; ++h) acc[h][mt] = M::mma(af, fl[h][4 * ks + g], acc[h][mt]);
+        for (int h = 0; h < HT; ++h) acc[h][mt] = M::mma(op[f % VW], b[h], acc[h][mt]);
+        ++f;
       }
     }
+    if constexpr (next && S::layout.chunk[s + 1] != c) {
+      store_ops(sop, c + 1, tid, opv);
+      __syncthreads();
+    }
   }
-  Update<N, real, BE> U;
-  U.load(A, k0, shot, nE, qout, res, tid);
-  __syncthreads();   // every wave is done with the flux buffer
+
+  // volume: three reference directions, K = Np (padded to a multiple of 4)
+  __device__ __forceinline__ void volume(const real *ops, real *sop, int tid) {
+    stagec::unroll<0, 3 * KS>([&](auto I) {
+      constexpr int s = decltype(I)::value, a = s / KS, ks = s % KS;
+      // rows past Np of the last k-step read a valid node and are zeroed
+      const int j = 4 * ks + g, jj = j < Np ? j : Np - 1;
+      step<s>(ops, sop, tid, [&](int h) {
+        const real v = C[h].c[a][0] * qf[h][0][jj] + C[h].c[a][1] * qf[h][1][jj] +
+                       C[h].c[a][2] * qf[h][2][jj];
+        return j < Np ? v : (real)0;
+      });
+    });
+  }
+  // lift: the column's flux on the 4 Nfp face nodes
+  __device__ __forceinline__ void lift(const real *ops, real *sop, int tid) {
+    stagec::unroll<0, S::KL>([&](auto I) {
+      constexpr int ks = decltype(I)::value;
+      step<3 * KS + ks>(ops, sop, tid, [&](int h) { return fl[h][4 * ks + g]; });
+    });
+  }
+
   // right-hand side to LDS in the block's (element, field, node) order
-  if (w < NT) {
+  __device__ __forceinline__ void store(real *out) const {
+    if (w >= NT) return;
 #pragma unroll
     for (int h = 0; h < HT; ++h) {
-      const int col = (w + h * NW) * 16 + (lane & 15);
-      if (col < 9 * nE) {
+      const int col = column(h);
+      if (col >= cols) continue;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+      for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int i = 16 * mt + M::row(g, r);
-            if (i < Np) sfl[col * Np + i] = acc[h][mt][r];
-          }
-      }
+        for (int r = 0; r < 4; ++r) {
+          const int i = (rows[mt] >> (8 * r)) & 255;
+          if (i < Np) out[col * Np + i] = acc[h][mt][r];
+        }
     }
   }
-  __syncthreads();
-  U.apply(A, sq, sfl, ssig, nE, src - k0, shot, step, tid);
-}
+};
 
 // Phase 3 on the vector ALUs: one thread per (element, node).  AN:
 // anisotropic elements, whose stress rate is C times the strain rate of the
@@ -594,15 +641,21 @@ struct StageGemm : SymGemm<N, 3, (9 * BE + 15) / 16, kThreads> {
   // a stress column's flux on face n is sum_m cf[n][m] dv_m with the same
   // coefficients as its volume term on Fscale_n n_n = -4 grad lambda_n, the
   // transform of cs; a velocity column's flux is stored as it is
-  __device__ __forceinline__ void face(double (&cf)[4][3]) const {
+  __device__ __forceinline__ void lift(const double *ops, double *sop, int tid) {
+    G::lift(ops, sop, tid, [&](double (&cf)[4][3]) {
 #pragma unroll
-    for (int m = 0; m < 3; ++m) {
-      const double c[4] = {0.0, G::cs[1][m], G::cs[2][m], G::cs[3][m]};
-      double t[4];
-      sym4(c, t);
+      for (int m = 0; m < 3; ++m) {
+        const double c[4] = {0.0, G::cs[1][m], G::cs[2][m], G::cs[3][m]};
+        double t[4];
+        sym4(c, t);
 #pragma unroll
-      for (int n = 0; n < 4; ++n) cf[n][m] = vel ? (double)(m == 0) : t[n];
-    }
+        for (int n = 0; n < 4; ++n) cf[n][m] = vel ? (double)(m == 0) : t[n];
+      }
+    });
+  }
+  // right-hand side to LDS in the block's (element, field, node) order
+  __device__ __forceinline__ void store(double *out) const {
+    G::store(out + G::column() * G::Np, ok);
   }
 };
 
@@ -859,8 +912,11 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
   __shared__ __attribute__((aligned(16))) real sfl[SF];
   __shared__ double smeta[BE * DGW_META];
   __shared__ double ssig[BE];
-  using SG = StageGemm<N, SY ? BE : 1, V == 3>;
-  __shared__ __attribute__((aligned(16))) double sop[SY ? SG::OPS : 2];
+  // the matrix-core form's GEMM
+  constexpr bool MC = V == 1 || V == 3;
+  using GM = std::conditional_t<SY, StageGemm<N, SY ? BE : 1, V == 3>,
+                                NodalGemm<N, real, MC && !SY ? BE : 1, V == 3>>;
+  __shared__ __attribute__((aligned(16))) real sop[MC ? GM::OPS : 4];
   const int slot = slot_of(item, nblk, total);
   const int shot = A.shot_map ? A.shot_map[slot] : slot;
   const int64_t step = A.shot_step[shot];
@@ -887,19 +943,19 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
   // in-bounds read of the first element that is never used), so no branch
   // makes the compiler wait on earlier loads
   // the first operator chunk
-  typename SG::vec2 opv[SG::OV];
-  if constexpr (SY) SG::load_ops(A.Asym, 0, tid, opv);
+  std::remove_reference_t<decltype(GM::op)> opv[GM::OV];
+  const real *ops = SY ? A.Asym : A.Anod;
+  if constexpr (MC) GM::load_ops(ops, 0, tid, opv);
   real qp[FI][9];
 #pragma unroll
   for (int u = 0; u < FI; ++u) {
 #pragma unroll
     for (int c = 0; c < 9; ++c) qp[u][c] = qin[T.gb[u] + c * Np];
   }
-  // The symmetry form reads its operators from LDS, so nothing waits behind the
-  // residual and it is loaded here.  In the nodal form every operator load
-  // would wait for it.
+  // The matrix-core forms read their operators from LDS, so nothing waits
+  // behind the residual and it is loaded here.
   Update<N, real, BE> U;
-  if constexpr (SY) U.load(A, k0, shot, nE, qout, res, tid);
+  if constexpr (MC) U.load(A, k0, shot, nE, qout, res, tid);
   // the block's own fields and per-element data (loads issued by
   // block_loads) to LDS
   {
@@ -924,18 +980,19 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
       }
     }
     if (tid < nE) ssig[tid] = B.sg;
-    if constexpr (SY) SG::store_ops(sop, 0, tid, opv);
+    if constexpr (MC) GM::store_ops(sop, 0, tid, opv);
   }
   __syncthreads();
 
   // ---- 2. faces: exact Riemann flux ----
-  // the nodes of this lane's orbits (sym.h), four to a word, and the first
-  // operator fragments, in flight during the flux
-  uint32_t nodes[Sym<N>::KS];
-  if constexpr (SY)
+  // the nodes of this lane's orbits (sym.h) or rows (nodal.h), four to a word
+  constexpr int TW = SY ? Sym<N>::KS : Nodal<N>::MT;
+  uint32_t nodes[TW];
+  if constexpr (MC) {
+    const uint32_t *tab = SY ? A.symnode : A.rowtab;
 #pragma unroll
-    for (int ks = 0; ks < Sym<N>::KS; ++ks)
-      nodes[ks] = A.symnode[4 * ks + ((tid & 63) >> 4)];
+    for (int u = 0; u < TW; ++u) nodes[u] = tab[4 * u + ((tid & 63) >> 4)];
+  }
 #pragma unroll
   for (int u = 0; u < FI; ++u) {
     const int t = tid + u * kThreads;
@@ -946,23 +1003,19 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
                           fm / Nfp, qp[u], d, ROW);
   }
   // ---- 3. volume, lift, update ----
-  if constexpr (SY) {
-    SG G(A, sq, sfl, sop, smeta, nE, k0, nodes, tid);
-    G.volume(A.Asym, sop, tid);
+  if constexpr (MC) {
+    GM G(A, sq, sfl, sop, smeta, nE, k0, nodes, tid);
+    G.volume(ops, sop, tid);
     __syncthreads();
-    G.lift(A.Asym, sop, tid, [&](double (&cf)[4][3]) { G.face(cf); });
+    G.lift(ops, sop, tid);
     __syncthreads();   // every wave is done with the flux buffer
-    G.store(sfl + G.column() * Np, G.ok);
+    G.store(sfl);
     __syncthreads();
     U.apply(A, sq, sfl, ssig, nE, src - k0, shot, step, tid);
   } else {
     __syncthreads();
-    if constexpr (V == 1 || V == 3)
-      phase3_mfma<N, real, BE, V == 3>(A, sq, sfl, smeta, ssig, nE, k0, shot, step, src, qout,
-                                       res, oz, tid);
-    else
-      phase3_nodes<N, real, BE, V == 2>(A, sq, sfl, smeta, ssig, nE, k0, shot, step, qout,
-                                        res, oz, tid);
+    phase3_nodes<N, real, BE, V == 2>(A, sq, sfl, smeta, ssig, nE, k0, shot, step, qout, res,
+                                      oz, tid);
   }
 }
 
@@ -1038,7 +1091,7 @@ hipError_t launch_t(int be, int wpc, int ncu, int nshots, const StageArgs<real> 
   constexpr int A_ = Shapes<N, real, V>::a, B_ = Shapes<N, real, V>::b;
   if (be != A_ && be != B_) return hipErrorInvalidValue;
   if ((V == 1 || V == 3) && (kSymForm<N, real> ? a.Asym == nullptr || a.nbsym == nullptr
-                                    : a.Avol == nullptr || a.Alift == nullptr))
+                                             : a.Anod == nullptr || a.rowtab == nullptr))
     return hipErrorInvalidValue;
   const int64_t nblk = (a.K + be - 1) / be;
   const int64_t total = nblk * nshots;

@@ -91,3 +91,18 @@ def test_layer_blocks(N, m):
     merr = rel_l2(s.pml_memory(0), m_ora.numpy()[el])
     say("N=%d layer elements %d fields %.3e memory %.3e" % (N, m, err, merr))
     assert err <= 1e-12 and merr <= 1e-12
+
+
+@pytest.mark.parametrize("N,n,kernel", [(1, 9, 1), (1, 10, 0), (2, 10, 1), (3, 8, 1), (3, 9, 0),
+                                        (4, 5, 0), (4, 6, 1), (4, 7, 0), (4, 9, 1), (5, 9, 1),
+                                        (5, 10, 0), (6, 4, 0), (6, 17, 1)])
+def test_fp32_kernel_is_not_timed(N, n, kernel):
+    """The FP32 kernel follows from order and size: both sides of each line."""
+    mesh = W.kuhn_cube(n)
+    K = mesh["etov"].shape[0]
+    s = Solver(N, 32, 1)
+    s.set_mesh_dict(mesh)
+    s.set_material(np.ones(K), np.ones(K), np.ones(K))
+    s.set_dt(1e-3)
+    assert s.autotune()[0] == kernel
+    s.close()
