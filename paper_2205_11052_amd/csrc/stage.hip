@@ -1019,9 +1019,16 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
   }
 }
 
+// Waves per SIMD that the registers have to leave room for.  At order 3 in FP64
+// the LDS holds four work-groups a CU: with 128 registers instead of 136 they
+// fit (48 -> 45 us, 24576 elements).  At order 4 it holds three, which the
+// registers do anyway.
+template <int N, typename real, int V>
+constexpr int kWaves = V == 1 && N == 3 && sizeof(real) == 8 ? 4 : 1;
+
 // One work-group per item.
 template <int N, typename real, int BE, int V>
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kThreads, (kWaves<N, real, V>))
 stage_kernel(StageArgs<real> A, int64_t nblk, int64_t total) {
   const int64_t item = xcd_item(blockIdx.x, total);
   FaceTab<N, BE> T;
