@@ -358,13 +358,68 @@ __global__ void __launch_bounds__(kPmlThreads) pml_kernel(PmlArgs<real> A) {
                           : n[b] * (Wv[c] * n[b] + n[c] * Wv[b] - n[c] * n[b] * nW);
     }
   }
-  LayerNode<N, real> L;
-  L.vel = vel;
-  L.k = k;
-  L.pi = pi;
-  L.i = i;
-  L.load(A, res, qout, mem, mres);
-  L.update(A, res, qout, mem, mres, g, Dg);
+  // every remaining load at once: the role's nine memory variables (phi for
+  // the stress role, psi for the velocity role) and their residuals, the
+  // node's profile, and the residual and output entries the role updates
+  // (stress components for the velocity role, velocity for the stress
+  // role; the stress role's last three slots repeat its first)
+  const int64_t mb = pi * 18 * Np + (vel ? 9 * Np : 0) + i;
+  const int nout = vel ? 6 : 3, fb = vel ? 3 : 0;
+  real mv[9], mr[9], db[3], ab[3], rv[6], ov[6];
+#pragma unroll
+  for (int w = 0; w < 9; ++w) mv[w] = mem[mb + w * Np];
+#pragma unroll
+  for (int w = 0; w < 9; ++w) mr[w] = mres[mb + w * Np];
+#pragma unroll
+  for (int b = 0; b < 3; ++b) {
+    db[b] = (real)A.prof[(pi * 6 + b) * Np + i];
+    ab[b] = (real)A.prof[(pi * 6 + 3 + b) * Np + i];
+  }
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    const int64_t idx = (k * 9 + fb + (c < nout ? c : 0)) * Np + i;
+    rv[c] = res[idx];
+    ov[c] = qout[idx];
+  }
+  const real ra = (real)A.rk_a, rb = (real)A.rk_b, rdt = (real)A.dt;
+  // the layer's terms: lambda tr(Psi) I + mu (Psi + Psi^T) on sigma
+  // (velocity role), or (1/rho) sum_b phi_cb on v_c (stress role)
+  real dl[6];
+  {
+    const real la = (real)g[M_LAM], mu = (real)g[M_MU], ri = (real)g[M_RHOINV];
+    const real tr = mv[0] + mv[4] + mv[8];
+    const real ds[6] = {la * tr + 2 * mu * mv[0], la * tr + 2 * mu * mv[4],
+                        la * tr + 2 * mu * mv[8], mu * (mv[5] + mv[7]),
+                        mu * (mv[2] + mv[6]), mu * (mv[1] + mv[3])};
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      const int cv = c < 3 ? c : 0;
+      const real dv = ri * (mv[3 * cv] + mv[3 * cv + 1] + mv[3 * cv + 2]);
+      dl[c] = vel ? ds[c] : dv;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    if (c < nout) {
+      const int64_t idx = (k * 9 + fb + c) * Np + i;
+      const real add = rdt * dl[c];
+      res[idx] = rv[c] + add;
+      qout[idx] = ov[c] + rb * add;
+    }
+  }
+  // memory update: m_t = -(d_b + alpha_b) m_cb - d_b (D or G)_cb; stage 1
+  // (a = 0) takes no part of mres, so stale values cannot leak in
+  const bool first = A.rk_a == 0.0;
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const int w = 3 * c + b;
+      const real rate = -(db[b] + ab[b]) * mv[w] - db[b] * Dg[c][b];
+      const real r = first ? rdt * rate : ra * mr[w] + rdt * rate;
+      mres[mb + w * Np] = r;
+      mem[mb + w * Np] = mv[w] + rb * r;
+    }
 }
 
 // The same in FP64 from order 3 with the derivatives and lifts on the matrix
