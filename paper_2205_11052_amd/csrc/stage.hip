@@ -271,8 +271,8 @@ __device__ __forceinline__ void column_setup(const StageArgs<real> &A, const dou
 // over the block's contiguous span, fully coalesced.
 // It is bound by the matrix instructions and the passes through LDS around
 // them.  FP32 stage launch, fragments of every tile from L2 -> this: order 4,
-// 82944 elements, 190 -> 164 us (without the fragment loads 112); order 5, 118
-// -> 96; order 6, 24576 elements, 223 -> 173 us.  A field that is not finite
+// 82944 elements, 190 -> 158 us (without the fragment loads 112); order 5, 118
+// -> 94; order 6, 24576 elements, 221 -> 169 us.  A field that is not finite
 // spreads over its element in a few stages, not within one, as zero tiles are
 // left out.
 template <int N, typename real, int BE, bool AN>
@@ -375,13 +375,24 @@ struct NodalGemm {
 
   // volume: three reference directions, K = Np (padded to a multiple of 4)
   __device__ __forceinline__ void volume(const real *ops, real *sop, int tid) {
-    stagec::unroll<0, 3 * KS>([&](auto I) {
-      constexpr int s = decltype(I)::value, a = s / KS, ks = s % KS;
+    // each value once from LDS for the three directions
+    real q[HT][3][KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
       // rows past Np of the last k-step read a valid node and are zeroed
       const int j = 4 * ks + g, jj = j < Np ? j : Np - 1;
+#pragma unroll
+      for (int h = 0; h < HT; ++h)
+#pragma unroll
+        for (int m = 0; m < 3; ++m) q[h][m][ks] = qf[h][m][jj];
+    }
+    stagec::unroll<0, 3 * KS>([&](auto I) {
+      constexpr int s = decltype(I)::value, a = s / KS, ks = s % KS;
+      const int j = 4 * ks + g;
       step<s>(ops, sop, tid, [&](int h) {
-        const real v = C[h].c[a][0] * qf[h][0][jj] + C[h].c[a][1] * qf[h][1][jj] +
-                       C[h].c[a][2] * qf[h][2][jj];
+        // written out: the bits must not hang on how a compiler contracts it
+        const real v = fma(C[h].c[a][2], q[h][2][ks],
+                           fma(C[h].c[a][0], q[h][0][ks], C[h].c[a][1] * q[h][1][ks]));
         return j < Np ? v : (real)0;
       });
     });
@@ -999,19 +1010,28 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
 #pragma unroll
     for (int u = 0; u < TW; ++u) nodes[u] = tab[4 * u + ((tid & 63) >> 4)];
   }
+  auto flux = [&] {
 #pragma unroll
-  for (int u = 0; u < FI; ++u) {
-    const int t = tid + u * kThreads;
-    if (t >= nE * NF) continue;
-    const int e = t / NF, fm = t - e * NF;
-    real *d = V == 0 || V == 2 ? sfl + t * 6 : sfl + e * (SY ? 6 : 9) * ROW + fm;
-    face_flux<N, real, V>(A, sq + e * 9 * Np, smeta + e * DGW_META, k0 + e, T.cn[u], T.n1[u],
-                          fm / Nfp, qp[u], d, ROW);
-  }
+    for (int u = 0; u < FI; ++u) {
+      const int t = tid + u * kThreads;
+      if (t >= nE * NF) continue;
+      const int e = t / NF, fm = t - e * NF;
+      real *d = V == 0 || V == 2 ? sfl + t * 6 : sfl + e * (SY ? 6 : 9) * ROW + fm;
+      face_flux<N, real, V>(A, sq + e * 9 * Np, smeta + e * DGW_META, k0 + e, T.cn[u], T.n1[u],
+                            fm / Nfp, qp[u], d, ROW);
+    }
+  };
   // ---- 3. volume, lift, update ----
   if constexpr (MC) {
     GM G(A, sq, sfl, sop, smeta, nE, k0, nodes, tid);
+    // In FP32 from order 4 on the flux, which waits for the neighbour traces,
+    // runs after the volume (order 4, 82944 elements, 162 -> 158 us).  FP64 has
+    // no registers to hold the traces that long (order 3 spills, order 4 loses
+    // a work-group a CU), and below order 4 nothing is gained.
+    constexpr bool late = V == 1 && N >= 4 && sizeof(real) == 4;
+    if constexpr (!late) flux();
     G.volume(ops, sop, tid);
+    if constexpr (late) flux();
     __syncthreads();
     G.lift(ops, sop, tid);
     if constexpr (N < 3) U.load(A, k0, shot, nE, qout, res, tid);
@@ -1020,6 +1040,7 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
     __syncthreads();
     U.apply(A, sq, sfl, ssig, nE, src - k0, shot, step, tid);
   } else {
+    flux();
     __syncthreads();
     phase3_nodes<N, real, BE, V == 2>(A, sq, sfl, smeta, ssig, nE, k0, shot, step, qout, res,
                                       oz, tid);
