@@ -1023,13 +1023,13 @@ __device__ __forceinline__ void stage_item(const StageArgs<real> &A, int64_t ite
   };
   // ---- 3. volume, lift, update ----
   if constexpr (MC) {
-    GM G(A, sq, sfl, sop, smeta, nE, k0, nodes, tid);
     // In FP32 from order 4 on the flux, which waits for the neighbour traces,
     // runs after the volume (order 4, 82944 elements, 162 -> 158 us).  FP64 has
     // no registers to hold the traces that long (order 3 spills, order 4 loses
     // a work-group a CU), and below order 4 nothing is gained.
     constexpr bool late = V == 1 && N >= 4 && sizeof(real) == 4;
     if constexpr (!late) flux();
+    GM G(A, sq, sfl, sop, smeta, nE, k0, nodes, tid);
     G.volume(ops, sop, tid);
     if constexpr (late) flux();
     __syncthreads();
