@@ -119,22 +119,29 @@ int dgw_ctx::download(void *dst, const void *src, size_t bytes) {
 // result.  Measured, host against device: 1 M values in 0.23 and 0.27 ms, out
 // 0.34 and 0.46 ms; 3.3 M in 1.05 and 0.81, out 1.50 and 1.51; 7.8 M in 2.96
 // and 2.27, out 6.1 and 6.3; 26 M (order 4, 82944 elements) in 24.9 and 7.6, out
-// 37.0 and 20.4.  Without the memory for a piece the host converts.
+// 37.0 and 20.4.  A piece lies in the residual, which no stage reads before it
+// has written it in the same step, so a transfer allocates nothing and uses
+// no memory that another stream may still work on.
 static constexpr size_t kPiece = size_t(1) << 22;       // values
 static constexpr size_t kDeviceIn = size_t(1) << 21, kDeviceOut = size_t(1) << 23;
 
+size_t dgw_ctx::piece(size_t n) const {   // values
+  return std::min({n, kPiece, (size_t)nshots * mesh.K * 9 * R.Np / 2});
+}
+
 int dgw_ctx::put_real(void *dst, const double *src, size_t n) {
   if (precision == 64) return upload(dst, src, sizeof(double) * n);
-  const size_t piece = std::min(n, kPiece);
-  if (n < kDeviceIn || !conv_scratch(piece)) {
+  if (n < kDeviceIn) {
     std::vector<float> tmp(src, src + n);
     return upload(dst, tmp.data(), sizeof(float) * n);
   }
-  for (size_t at = 0; at < n; at += piece) {
-    const size_t m = std::min(piece, n - at);
-    hipError_t e = hipMemcpyAsync(d_conv, src + at, sizeof(double) * m, hipMemcpyHostToDevice,
+  double *conv = (double *)d_res;
+  const size_t step = piece(n);
+  for (size_t at = 0; at < n; at += step) {
+    const size_t m = std::min(step, n - at);
+    hipError_t e = hipMemcpyAsync(conv, src + at, sizeof(double) * m, hipMemcpyHostToDevice,
                                   stream);
-    if (e == hipSuccess) e = launch_narrow(d_conv, (float *)dst + at, (int64_t)m, stream);
+    if (e == hipSuccess) e = launch_narrow(conv, (float *)dst + at, (int64_t)m, stream);
     if (e != hipSuccess) {
       (void)hipStreamSynchronize(stream);
       return hipfail(e, "FP32 upload");
@@ -146,18 +153,19 @@ int dgw_ctx::put_real(void *dst, const double *src, size_t n) {
 
 int dgw_ctx::get_real(double *dst, const void *src, size_t n) {
   if (precision == 64) return download(dst, src, sizeof(double) * n);
-  const size_t piece = std::min(n, kPiece);
-  if (n < kDeviceOut || !conv_scratch(piece)) {
+  if (n < kDeviceOut) {
     std::vector<float> tmp(n);
     const int rc = download(tmp.data(), src, sizeof(float) * n);
     for (size_t i = 0; rc == DGW_OK && i < n; ++i) dst[i] = tmp[i];
     return rc;
   }
-  for (size_t at = 0; at < n; at += piece) {
-    const size_t m = std::min(piece, n - at);
-    hipError_t e = launch_widen((const float *)src + at, d_conv, (int64_t)m, stream);
+  double *conv = (double *)d_res;
+  const size_t step = piece(n);
+  for (size_t at = 0; at < n; at += step) {
+    const size_t m = std::min(step, n - at);
+    hipError_t e = launch_widen((const float *)src + at, conv, (int64_t)m, stream);
     if (e == hipSuccess)
-      e = hipMemcpyAsync(dst + at, d_conv, sizeof(double) * m, hipMemcpyDeviceToHost, stream);
+      e = hipMemcpyAsync(dst + at, conv, sizeof(double) * m, hipMemcpyDeviceToHost, stream);
     if (e != hipSuccess) {
       (void)hipStreamSynchronize(stream);
       return hipfail(e, "FP32 download");
@@ -165,16 +173,6 @@ int dgw_ctx::get_real(double *dst, const void *src, size_t n) {
   }
   hipError_t e = hipStreamSynchronize(stream);
   return e == hipSuccess ? DGW_OK : hipfail(e, "hipStreamSynchronize");
-}
-
-bool dgw_ctx::conv_scratch(size_t n) {
-  if (n > conv_n) {
-    (void)hipStreamSynchronize(stream);
-    dfree(d_conv);
-    d_conv = (double *)dalloc(sizeof(double) * n);
-    conv_n = d_conv ? n : 0;
-  }
-  return d_conv != nullptr;
 }
 
 size_t dgw_ctx::real_size() const { return precision == 64 ? 8 : 4; }

@@ -74,7 +74,7 @@ struct dgw_ctx {
   uint8_t *d_nbsym = nullptr;
   double *d_M = nullptr;
   void *d_q[2] = {nullptr, nullptr};
-  void *d_res = nullptr;
+  void *d_res = nullptr;            // read from the second stage of a step on only
   int cur = 0;                      // buffer the next step reads from
   std::vector<int> loc;             // per shot: buffer holding its state
   int64_t *d_step = nullptr, *d_len = nullptr;
@@ -89,8 +89,6 @@ struct dgw_ctx {
   double *d_rec_w = nullptr, *d_trace = nullptr;
   std::vector<int32_t> h_nrec, h_rec_elem;
   std::vector<double> h_rec_w;
-  double *d_conv = nullptr;         // [conv_n] piece of a converted transfer (FP32)
-  size_t conv_n = 0;
   double *d_partial = nullptr;
   int *d_flag = nullptr;
 
@@ -159,7 +157,7 @@ struct dgw_ctx {
   size_t real_size() const;
   int put_real(void *dst, const double *src, size_t n);        // host FP64 -> reals
   int get_real(double *dst, const void *src, size_t n);        // reals -> host FP64
-  bool conv_scratch(size_t n);
+  size_t piece(size_t n) const;                                // of a converted transfer
   void invalidate_graph();
   int upload_operators();
   int alloc_shots();
