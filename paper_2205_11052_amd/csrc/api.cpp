@@ -62,7 +62,10 @@ void *dgw_ctx::dalloc(size_t bytes) {
   } else if (hipMalloc(&p, bytes) != hipSuccess) {
     p = nullptr;
   }
-  if (p) owned.push_back(p);
+  if (p)
+    owned.push_back(p);
+  else
+    (void)hipGetLastError();   // reported by the caller, not by the next launch
   return p;
 }
 
