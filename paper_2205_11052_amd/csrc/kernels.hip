@@ -121,9 +121,11 @@ template <typename A, typename B>
 hipError_t launch_convert(const A *in, B *out, int64_t n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   const int64_t nb = (n + 255) / 256;
-  hipLaunchKernelGGL((convert_kernel<A, B>), dim3((unsigned)(nb < 4096 ? nb : 4096)), dim3(256),
-                     0, st, in, out, n);
-  return hipGetLastError();
+  // the launch's own status: a transfer doesn't report a failed call that was
+  // made elsewhere
+  void *args[] = {&in, &out, &n};
+  return hipLaunchKernel((const void *)convert_kernel<A, B>,
+                         dim3((unsigned)(nb < 4096 ? nb : 4096)), dim3(256), args, 0, st);
 }
 
 hipError_t launch_narrow(const double *in, float *out, int64_t n, hipStream_t st) {

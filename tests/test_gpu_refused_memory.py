@@ -1,5 +1,5 @@
 """Failed device allocations are reported once, by the call that made them: the
-launches that follow succeed."""
+launches that follow succeed, and a transfer doesn't report one made elsewhere."""
 
 import ctypes as C
 
@@ -53,4 +53,23 @@ def test_refused_scratch_is_not_the_next_launch_s_error():
     say("case step after it")
     s.step(1)
     s.check_finite()
+    s.close()
+
+
+def test_transfer_does_not_report_another_call_s_failure():
+    mesh = W.kuhn_cube(13)              # 10 M values: converted on the device both ways
+    K = mesh["etov"].shape[0]
+    s = Solver(6, 32, 1)
+    s.set_mesh_dict(mesh)
+    q = np.random.default_rng(2).standard_normal((K, 9, s.Np))
+    fail_malloc()
+    try:
+        s.set_fields(0, q)
+        got = s.get_fields(0)
+    finally:
+        last = _lib.load().hipGetLastError
+        last.restype = C.c_int
+        left = last()                   # still the caller's to see
+    assert left != 0
+    np.testing.assert_array_equal(got, q.astype(np.float32))
     s.close()
