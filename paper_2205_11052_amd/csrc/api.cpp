@@ -192,12 +192,10 @@ static std::vector<real> convert(const std::vector<double> &v) {
   return std::vector<real>(v.begin(), v.end());
 }
 
-template <typename real>
-static std::vector<real> transpose(const std::vector<double> &A, int rows,
-                                   int cols) {
-  std::vector<real> T((size_t)rows * cols);
+static std::vector<double> transpose(const std::vector<double> &A, int rows, int cols) {
+  std::vector<double> T((size_t)rows * cols);
   for (int i = 0; i < rows; ++i)
-    for (int j = 0; j < cols; ++j) T[(size_t)j * rows + i] = (real)A[(size_t)i * cols + j];
+    for (int j = 0; j < cols; ++j) T[(size_t)j * rows + i] = A[(size_t)i * cols + j];
   return T;
 }
 
@@ -300,38 +298,34 @@ static void nodal_tables(const RefElem &R, int precision, std::vector<double> &f
       }
 }
 
+// Operator tables, in one allocation and one upload: those that the kernels of
+// this order and precision read, no others.
 int dgw_ctx::upload_operators() {
-  const int Np = R.Np, NF = 4 * R.Nfp;
-  const size_t rs = real_size();
-  d_DrT = dalloc(rs * Np * Np);
-  d_DsT = dalloc(rs * Np * Np);
-  d_DtT = dalloc(rs * Np * Np);
-  d_LIFTT = dalloc(rs * Np * NF);
-  d_fmask = (int32_t *)dalloc(sizeof(int32_t) * NF);
-  d_M = (double *)dalloc(sizeof(double) * Np * Np);
-  if (!d_DrT || !d_DsT || !d_DtT || !d_LIFTT || !d_fmask || !d_M)
-    return fail(DGW_ENOMEM, "device allocation failed (operators)");
-  int rc;
-  if (precision == 64) {
-    auto a = transpose<double>(R.Dr, Np, Np), b = transpose<double>(R.Ds, Np, Np),
-         c = transpose<double>(R.Dt, Np, Np), l = transpose<double>(R.LIFT, Np, NF);
-    if ((rc = upload(d_DrT, a.data(), rs * a.size()))) return rc;
-    if ((rc = upload(d_DsT, b.data(), rs * b.size()))) return rc;
-    if ((rc = upload(d_DtT, c.data(), rs * c.size()))) return rc;
-    if ((rc = upload(d_LIFTT, l.data(), rs * l.size()))) return rc;
-  } else {
-    auto a = transpose<float>(R.Dr, Np, Np), b = transpose<float>(R.Ds, Np, Np),
-         c = transpose<float>(R.Dt, Np, Np), l = transpose<float>(R.LIFT, Np, NF);
-    if ((rc = upload(d_DrT, a.data(), rs * a.size()))) return rc;
-    if ((rc = upload(d_DsT, b.data(), rs * b.size()))) return rc;
-    if ((rc = upload(d_DtT, c.data(), rs * c.size()))) return rc;
-    if ((rc = upload(d_LIFTT, l.data(), rs * l.size()))) return rc;
-  }
-  // operator fragments for the matrix-core stage kernel, in MFMA lane
-  // order (lane l of a 16x4 tile holds row l % 16, column l / 16), zero
-  // outside the operator: Avol[a][ks][mt][l] = D_a[16 mt + l % 16][4 ks +
+  const int N = R.N, Np = R.Np, NF = 4 * R.Nfp;
+  std::vector<char> host;
+  auto put = [&](const void *src, size_t bytes) {   // offset of the table
+    const size_t at = (host.size() + 255) / 256 * 256;
+    host.resize(at + bytes);
+    std::memcpy(host.data() + at, src, bytes);
+    return at;
+  };
+  auto put_reals = [&](const std::vector<double> &v) {
+    if (precision == 64) return put(v.data(), sizeof(double) * v.size());
+    const std::vector<float> f(v.begin(), v.end());
+    return put(f.data(), sizeof(float) * f.size());
+  };
+  const size_t dr = put_reals(transpose(R.Dr, Np, Np)), ds = put_reals(transpose(R.Ds, Np, Np)),
+               dt = put_reals(transpose(R.Dt, Np, Np)),
+               lf = put_reals(transpose(R.LIFT, Np, NF));
+  const std::vector<int32_t> fmask(R.fmask.begin(), R.fmask.end());
+  const size_t fm = put(fmask.data(), sizeof(int32_t) * fmask.size()),
+               mm = put(R.M.data(), sizeof(double) * R.M.size());
+  // kernel 2's fragments, in MFMA lane order (lane l of a 16x4 tile holds
+  // row l % 16, column l / 16), zero outside the operator: Avol[a][ks][mt][l] = D_a[16 mt + l % 16][4 ks +
   // l / 16] and Alift[ks][mt][l] = LIFT[16 mt + l % 16][4 ks + l / 16]
-  {
+  const bool split = stage_kernel_supported(2, N, precision);
+  size_t vol = 0, lift = 0, alf = 0;
+  if (split) {
     const int MT = (Np + 15) / 16, KS = (Np + 3) / 4, KL = NF / 4;
     std::vector<double> av((size_t)3 * KS * MT * 64, 0.0), al((size_t)KL * MT * 64, 0.0);
     const std::vector<double> *D[3] = {&R.Dr, &R.Ds, &R.Dt};
@@ -364,75 +358,64 @@ int dgw_ctx::upload_operators() {
               af[(((size_t)f * KF + ks) * MT + mt) * 64 + l] =
                   (f == 0 ? 2.0 : -2.0) * R.LIFT[(size_t)i * NF + f * Nfp + m];
           }
-    d_Avol = dalloc(rs * av.size());
-    d_Alift = dalloc(rs * al.size());
-    d_Alf = dalloc(rs * af.size());
-    if (!d_Avol || !d_Alift || !d_Alf)
-      return fail(DGW_ENOMEM, "device allocation failed (operators)");
-    if (precision == 64) {
-      if ((rc = upload(d_Avol, av.data(), rs * av.size()))) return rc;
-      if ((rc = upload(d_Alift, al.data(), rs * al.size()))) return rc;
-      if ((rc = upload(d_Alf, af.data(), rs * af.size()))) return rc;
-    } else {
-      std::vector<float> avf(av.begin(), av.end()), alf(al.begin(), al.end()),
-          aff(af.begin(), af.end());
-      if ((rc = upload(d_Avol, avf.data(), rs * avf.size()))) return rc;
-      if ((rc = upload(d_Alift, alf.data(), rs * alf.size()))) return rc;
-      if ((rc = upload(d_Alf, aff.data(), rs * aff.size()))) return rc;
-    }
+    vol = put_reals(av);
+    lift = put_reals(al);
+    alf = put_reals(af);
   }
-  {
-    std::vector<double> fr;
-    std::vector<uint32_t> rows;
-    switch (R.N) {
-      case 1: nodal_tables<1>(R, precision, fr, rows); break;
-      case 2: nodal_tables<2>(R, precision, fr, rows); break;
-      case 3: nodal_tables<3>(R, precision, fr, rows); break;
-      case 4: nodal_tables<4>(R, precision, fr, rows); break;
-      case 5: nodal_tables<5>(R, precision, fr, rows); break;
-      default: nodal_tables<6>(R, precision, fr, rows); break;
-    }
-    d_Anod = dalloc(rs * fr.size());
-    d_rowtab = (uint32_t *)dalloc(sizeof(uint32_t) * rows.size());
-    if (!d_Anod || !d_rowtab) return fail(DGW_ENOMEM, "device allocation failed (operators)");
-    const std::vector<float> f32(fr.begin(), fr.end());
-    if ((rc = upload(d_Anod, precision == 64 ? (const void *)fr.data() : f32.data(),
-                     rs * fr.size())))
-      return rc;
-    if ((rc = upload(d_rowtab, rows.data(), sizeof(uint32_t) * rows.size()))) return rc;
-  }
-  if (precision == 64) {
-    std::vector<double> fr;
-    std::vector<uint32_t> nd;
-    std::vector<int32_t> order;
-    switch (R.N) {
-      case 1: sym_tables<1>(R, fr, nd, order); break;
-      case 2: sym_tables<2>(R, fr, nd, order); break;
+  // kernel 1's (and the FP64 layer kernel's from order 3): symmetry components
+  // or nodal form
+  const bool sym = stage_symmetric(N, precision);
+  std::vector<double> fr;
+  std::vector<uint32_t> nd;
+  std::vector<int32_t> order;
+  if (sym)
+    switch (N) {
       case 3: sym_tables<3>(R, fr, nd, order); break;
       case 4: sym_tables<4>(R, fr, nd, order); break;
       case 5: sym_tables<5>(R, fr, nd, order); break;
       default: sym_tables<6>(R, fr, nd, order); break;
     }
+  else
+    switch (N) {
+      case 1: nodal_tables<1>(R, precision, fr, nd); break;
+      case 2: nodal_tables<2>(R, precision, fr, nd); break;
+      case 3: nodal_tables<3>(R, precision, fr, nd); break;
+      case 4: nodal_tables<4>(R, precision, fr, nd); break;
+      case 5: nodal_tables<5>(R, precision, fr, nd); break;
+      default: nodal_tables<6>(R, precision, fr, nd); break;
+    }
+  const size_t frag = put_reals(fr), node = put(nd.data(), sizeof(uint32_t) * nd.size());
+  size_t fsym = 0;
+  if (sym) {
     std::vector<int32_t> fs(NF);
-    std::vector<uint8_t> nb((size_t)mesh.K * NF);
     for (int t = 0; t < NF; ++t) fs[t] = R.fmask[order[t]];
-    for (int64_t k = 0; k < mesh.K; ++k)
-      for (int t = 0; t < NF; ++t) nb[k * NF + t] = mesh.nbnode[k * NF + order[t]];
-    d_Asym = dalloc(sizeof(double) * fr.size());
-    d_symnode = (uint32_t *)dalloc(sizeof(uint32_t) * nd.size());
-    d_fsym = (int32_t *)dalloc(sizeof(int32_t) * NF);
-    d_nbsym = (uint8_t *)dalloc(nb.size());
-    if (!d_Asym || !d_symnode || !d_fsym || !d_nbsym)
-      return fail(DGW_ENOMEM, "device allocation failed (operators)");
-    if ((rc = upload(d_Asym, fr.data(), sizeof(double) * fr.size()))) return rc;
-    if ((rc = upload(d_symnode, nd.data(), sizeof(uint32_t) * nd.size()))) return rc;
-    if ((rc = upload(d_fsym, fs.data(), sizeof(int32_t) * NF))) return rc;
-    if ((rc = upload(d_nbsym, nb.data(), nb.size()))) return rc;
+    fsym = put(fs.data(), sizeof(int32_t) * NF);
   }
-  std::vector<int32_t> fm(R.fmask.begin(), R.fmask.end());
-  if ((rc = upload(d_fmask, fm.data(), sizeof(int32_t) * fm.size()))) return rc;
-  if ((rc = upload(d_M, R.M.data(), sizeof(double) * R.M.size()))) return rc;
-  return DGW_OK;
+  char *dev = (char *)dalloc(host.size());
+  if (!dev) return fail(DGW_ENOMEM, "device allocation failed (operators)");
+  d_DrT = dev + dr;
+  d_DsT = dev + ds;
+  d_DtT = dev + dt;
+  d_LIFTT = dev + lf;
+  d_fmask = (int32_t *)(dev + fm);
+  d_M = (double *)(dev + mm);
+  if (split) {
+    d_Avol = dev + vol;
+    d_Alift = dev + lift;
+    d_Alf = dev + alf;
+  }
+  (sym ? d_Asym : d_Anod) = dev + frag;
+  (sym ? d_symnode : d_rowtab) = (uint32_t *)(dev + node);
+  if (sym) d_fsym = (int32_t *)(dev + fsym);
+  int rc;
+  if ((rc = upload(dev, host.data(), host.size()))) return rc;
+  if (!sym) return DGW_OK;
+  std::vector<uint8_t> nb((size_t)mesh.K * NF);
+  for (int64_t k = 0; k < mesh.K; ++k)
+    for (int t = 0; t < NF; ++t) nb[k * NF + t] = mesh.nbnode[k * NF + order[t]];
+  d_nbsym = (uint8_t *)dalloc(nb.size());
+  if (!d_nbsym) return fail(DGW_ENOMEM, "device allocation failed (operators)");
+  return upload(d_nbsym, nb.data(), nb.size());
 }
 
 int dgw_ctx::alloc_shots() {

@@ -64,7 +64,7 @@ struct dgw_ctx {
   int32_t *d_conn = nullptr, *d_nbtab = nullptr, *d_fmask = nullptr;
   uint8_t *d_nbnode = nullptr, *d_nbfnode = nullptr;
   void *d_DrT = nullptr, *d_DsT = nullptr, *d_DtT = nullptr, *d_LIFTT = nullptr;
-  void *d_Avol = nullptr, *d_Alift = nullptr;   // MFMA operator fragments
+  void *d_Avol = nullptr, *d_Alift = nullptr;   // fragments of kernel 2
   void *d_Alf = nullptr;                         // per-face lift fragments
   void *d_Asym = nullptr;                        // symmetry-component fragments (sym.h)
   uint32_t *d_symnode = nullptr;

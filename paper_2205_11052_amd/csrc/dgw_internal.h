@@ -251,6 +251,11 @@ hipError_t launch_set_steps(int64_t *steps, int nshots, int64_t value,
 hipError_t launch_stage(int kernel, int N, int precision, int be, int wpc,
                         int ncu, int nshots, const void *args, hipStream_t st);
 bool stage_kernel_supported(int kernel, int N, int precision);
+// Whether kernel 1 of an order and precision works in symmetry components
+// (sym.h), and the layer kernel with it; else it has the nodal form (nodal.h).
+// FP32 keeps the nodal form's order of summation, and with it its results to
+// the last bit.
+constexpr bool stage_symmetric(int N, int precision) { return precision == 64 && N >= 3; }
 // Whether kernel 0 of an order and precision runs kernel 1's code.
 bool stage_zero_is_one(int N, int precision);
 // Kernel 2 (stage_split.hip): the minimal-form matrix-core kernel, 16

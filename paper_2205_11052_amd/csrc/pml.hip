@@ -605,7 +605,7 @@ __global__ void __launch_bounds__(kPmlThreads, 4) pml_sym_kernel(PmlArgs<double>
 
 template <int N, typename real>
 hipError_t launch_n(const PmlArgs<real> &a, int nshots, hipStream_t st) {
-  if constexpr (sizeof(real) == 8 && N >= 3) {
+  if constexpr (stage_symmetric(N, 8 * (int)sizeof(real))) {
     constexpr int PB = PmlSym<N>::PB;
     const dim3 grid((unsigned)((a.nP + PB - 1) / PB), (unsigned)nshots);
     hipLaunchKernelGGL(pml_sym_kernel<N>, grid, dim3(kPmlThreads), 0, st, a);

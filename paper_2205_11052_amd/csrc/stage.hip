@@ -47,11 +47,9 @@ namespace dgw {
 namespace {
 
 constexpr int kThreads = 256;
-// Whether the matrix-core form of a precision works in symmetry components
-// (StageGemm): FP64.  FP32 keeps the nodal form's order of summation, and with
-// it its results to the last bit.
+// Whether the matrix-core form works in symmetry components (StageGemm).
 template <int N, typename real>
-constexpr bool kSymForm = N >= 3 && sizeof(real) == 8;
+constexpr bool kSymForm = stage_symmetric(N, 8 * (int)sizeof(real));
 using namespace stagec;
 
 // Residual and update of a block's contiguous span by 16-byte vectors; the
