@@ -273,8 +273,10 @@ int dgw_set_adjoint_memory(dgw_ctx *ctx, int64_t bytes);
  * from / written to that JSON file (keyed by order, precision, element count
  * and shot count).  The chosen shape is returned through the two pointers
  * (either may be NULL); see dgw_set_launch.  In FP32, where the kernels round
- * differently, the kernel follows from the order and the element and shot
- * counts and only its shape is timed. */
+ * differently, on a device of 256 compute units the kernel follows from the
+ * order and the number of elements of all shots together and only its shape is
+ * timed; on other devices every kernel is.  A choice read from the file is
+ * taken as it stands, whichever kernel it names. */
 int dgw_autotune(dgw_ctx *ctx, const char *cache_path, int *kernel,
                  int *elems_per_block, int *wgs_per_cu);
 

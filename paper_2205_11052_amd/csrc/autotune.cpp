@@ -1,17 +1,17 @@
 // Launch-shape autotuner of the stage kernel.
 //
-// Every implemented launch shape -- the node-per-thread kernel with each
-// elements-per-work-group value x work-groups per compute unit of the
-// persistent grid (0 meaning one work-group per block of elements), and the
-// lane-per-field kernel where it supports the order -- is timed with HIP events on the
-// context's stream over real stage launches of the context's own workload,
-// writing into scratch buffers so the solver state is untouched.  The fastest
-// shape is kept; with a cache path the choice is stored in a flat JSON object
-// keyed by order, precision, element count and shot count, and read back on
-// later calls instead of timing again.
+// The launch shapes -- kernels 0 and 1 with each elements-per-work-group
+// value x work-groups per compute unit of the persistent grid (0 meaning one
+// work-group per block of elements), and kernel 2 where it supports the order
+// -- are timed with HIP events on the context's stream over real stage launches
+// of the context's own workload, writing into scratch buffers so the solver
+// state is untouched.  Left out are kernel 0 where it runs kernel 1's code
+// (FP64 from order 2) and, in FP32, the kernels that tuner_rule.h doesn't name.
+// The fastest shape is kept; with a cache path the choice is stored in a flat
+// JSON object keyed by order, precision, element count and shot count, and read
+// back on later calls instead of timing again, whichever kernel it names.
 #include <hip/hip_runtime.h>
 
-#include <cstdint>
 #include <cstdio>
 #include <fstream>
 #include <map>
@@ -20,6 +20,7 @@
 
 #include "../../include/dgw.h"
 #include "dgw_ctx.h"
+#include "tuner_rule.h"
 
 using namespace dgw;
 
@@ -57,36 +58,6 @@ bool write_cache(const char *path, const std::map<std::string, long> &m) {
   }
   f << "\n}\n";
   return (bool)f;
-}
-
-
-// The FP32 kernels round differently (relative 1e-6 after some hundred stages),
-// so FP32 doesn't time one against the other: the kernel follows from the order
-// and the elements of all shots, and only its launch shape is timed.  Kernel 0
-// runs where it is named here, kernel 1 elsewhere.  The lines are where the two
-// took the same time over 48 to 82944 elements while kernel 1 still read every
-// operator tile from L2 (order 6: 24576 elements, 201 against 221 us; order 3:
-// 24576 elements, 31 against 35; order 1: 82944 elements, 28 against 38; the
-// middle ranges are where kernel 1's last wave of work-groups was nearly
-// empty), and stay there although kernel 1 has become faster (order 6: 173),
-// so that a run gives the bits it gave.
-struct Range {
-  int N;
-  bool aniso;
-  int64_t from, to;
-};
-constexpr int64_t kEnd = INT64_MAX;
-constexpr Range kNodePerThread[] = {
-    {1, false, 5100, kEnd}, {3, false, 3700, kEnd}, {4, false, 0, 1000},
-    {4, false, 1650, 3700}, {5, false, 5100, 9100}, {6, false, 0, 29000},
-    {1, true, 3700, kEnd},  {2, true, 1650, kEnd},  {3, true, 0, kEnd},
-    {4, true, 1650, 2500},  {5, true, 0, 530},      {5, true, 1000, 1650},
-    {6, true, 0, 20000}};
-
-int fp32_kernel(int N, bool aniso, int64_t elems) {
-  for (const Range &r : kNodePerThread)
-    if (r.N == N && r.aniso == aniso && elems >= r.from && elems < r.to) return 0;
-  return 1;
 }
 
 }  // namespace
@@ -148,8 +119,8 @@ extern "C" int dgw_autotune(dgw_ctx *c, const char *cache_path, int *kernel,
     for (const auto &o : opts) {
       // (a stored choice of any kernel is still taken from the cache above)
       if (o.kernel == 0 && stage_zero_is_one(c->R.N, c->precision)) continue;
-      if (c->precision == 32 &&
-          o.kernel != fp32_kernel(c->R.N, c->have_aniso, c->mesh.K * c->nshots))
+      if (!tuner_times(o.kernel, c->R.N, c->precision, c->have_aniso,
+                       c->mesh.K * c->nshots, c->ncu))
         continue;
       hipError_t err = hipSuccess;
       const int reps = 10;
