@@ -91,7 +91,9 @@ __device__ __forceinline__ void flux_changes(const PmlArgs<real> &A, const real 
 
 // The last phase of a (layer element, node) and role: the velocity role
 // (vel) holds the memory psi and updates the stresses, the stress role holds phi
-// and updates the velocities.
+// and updates the velocities.  pml_kernel has the same phase in place: through
+// this struct the compiler contracts its FP32 sums otherwise, which changes its
+// results in the last bits.
 template <int N, typename real>
 struct LayerNode {
   static constexpr int Np = Sz<N>::Np;
@@ -434,7 +436,10 @@ __global__ void __launch_bounds__(kPmlThreads) pml_kernel(PmlArgs<real> A) {
 // layer elements, FP64): 482 -> 295 us a launch, 1.47 GB at 5.0 of the 5.3 TB/s
 // that a copy reaches (the vector form read 390 LDS values a thread); order 3,
 // 12480 layer elements, 71 -> 57 us; order 5, 6528 of them, 144 -> 101 us; order
-// 6, 2960 of them, 126 -> 78 us.
+// 6, 2960 of them, 126 -> 78 us.  The bound of four waves a SIMD (two
+// work-groups a CU) costs no spills at orders 3 and 4 (114 and 120 registers), 5
+// at order 5 (24 bytes a lane) and 42 at order 6 (84 bytes), whose times include
+// them; they were not measured without the bound.
 template <int N>
 struct PmlSym {
   static constexpr int Np = Sz<N>::Np;

@@ -270,9 +270,9 @@ __device__ __forceinline__ void column_setup(const StageArgs<real> &A, const dou
 // It is bound by the matrix instructions and the passes through LDS around
 // them.  FP32 stage launch, fragments of every tile from L2 -> this: order 4,
 // 82944 elements, 190 -> 158 us (without the fragment loads 112); order 5, 118
-// -> 94; order 6, 24576 elements, 221 -> 169 us.  A field that is not finite
-// spreads over its element in a few stages, not within one, as zero tiles are
-// left out.
+// -> 94; order 6, 24576 elements, 221 -> 169 us.  A value that is not finite
+// spreads over its element in a few stages instead of one, as zero tiles are
+// left out; after a whole step the values that are not finite are the same.
 template <int N, typename real, int BE, bool AN>
 struct NodalGemm {
   using S = Nodal<N>;
@@ -1086,9 +1086,17 @@ stage_kernel_persistent(StageArgs<real> A, int64_t nblk, int64_t total) {
 }
 
 // Elements per work-group for variant V: the largest BE with one thread per
-// element node (V = 0: BE * Np <= 256) or one MFMA column per (element,
-// field) (V = 1: 9 BE <= 64, four waves of 16 columns), with the LDS tile
-// (fields, lifted flux, per-element data) within 64 KB; and half of it.
+// element node (V = 0, 2: BE * Np <= 256) or one MFMA column per (element,
+// field) (V = 1, 3: 9 BE <= 64, four waves of 16 columns) for which the fields,
+// the lifted quantities (six per face node, nine in V = 1 and 3) and the
+// per-element data take at most 64 KB; and half of it.  That sum was the
+// nodal form's LDS in FP64 when its operators came from L2, and the blocks are
+// part of the launch shapes that callers set and tuners store, so it stays
+// the rule; it is not the LDS of every form.  The symmetry components
+// store six quantities and stage their operators beside them (order 4, 7
+// elements, 53,176 bytes; order 5, 6 elements, 63,312; order 6, 4 elements,
+// 69,920), the FP32 nodal form stages its fragments (order 4, 14 elements,
+// 65,664; order 6, 7 elements, 70,568).
 template <int N, typename real, int V>
 struct Shapes {
   static constexpr int Np = Sz<N>::Np, NF = 4 * Sz<N>::Nfp;
@@ -1098,10 +1106,9 @@ struct Shapes {
       V == 0 || V == 2 ? kThreads / Np : kThreads / 64 * 16 / 9;
   static constexpr int cap2 = 65536 / per;
   static constexpr int a0 = cap1 < cap2 ? cap1 : cap2;
-  // matrix-core FP32: two column tiles per wave (14 elements) where the LDS
-  // tile fits, and the one-tile block as the second choice (the isotropic
-  // form feeds both tiles from each operator fragment, the anisotropic form
-  // runs them one after the other); the two share their block choices
+  // matrix-core FP32: two column tiles per wave (14 elements), both fed from
+  // each operator fragment, where the sum above allows it, and the one-tile
+  // block as the second choice
   static constexpr bool two = (V == 1 || V == 3) && sizeof(real) == 4 && cap2 >= 2 * cap1;
   static constexpr int a = two ? 2 * cap1 : a0;
   static constexpr int b = two ? cap1 : (a0 / 2 > 0 ? a0 / 2 : 1);
